@@ -88,14 +88,19 @@ typedef struct {
     uint64_t hbm_budget_bytes; /* 0: 80 % of the device memory free at tvs_create */
     int32_t device;          /* HIP device ordinal */
     int32_t max_tries;       /* bound on the retries of one checked TV step; 0: 100000 */
-    int32_t sweep_kernel;    /* 0 or 1: one launch per DROP block (finish the previous block
+    int32_t sweep_kernel;    /* 0: the library's choice: many DROP blocks per launch by
+                                workgroups that stay on the device, where the image's
+                                crossed tiles fit its LDS, else as 1;
+                                1: one launch per DROP block (finish the previous block
                                 and form this block's dot products, tile by tile);
-                                2: the same work in two launches per block */
-    int32_t tile_threads;    /* threads per image-tile workgroup of the DROP kernels
-                                (64, 128, 256); 0: 128 on the fly and for grids of
+                                2: the same work in two launches per block.
+                                The images are the same */
+    int32_t tile_threads;    /* threads per image-tile workgroup of the per-block launches
+                                (64, 128, 256; sweep_kernel 0 is then read as 1); 0: 128 on the fly and for grids of
                                 more than 16 image tiles per CU, else 256 */
     int32_t time_sample;     /* k > 0: kernel-stamped HIP events on the launches of every
-                                k-th DROP block (per-launch durations in tvs_stats); 0: off */
+                                k-th DROP block, or events around every launch of many
+                                blocks (durations per block in tvs_stats); 0: off */
     int32_t fill_wgs_per_cu; /* on-the-fly rows: cap on the workgroups per compute unit of
                                 the row formation that runs beside the DROP chain; 0 or < 0:
                                 no cap */

@@ -21,6 +21,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 SOURCES = {
     "rows.hip": ["-ffp-contract=off"],
     "drop.hip": ["-ffp-contract=off"],
+    "chain.hip": ["-ffp-contract=off"],
     "tv.hip": ["-ffp-contract=off"],
     "batch.hip": ["-ffp-contract=off"],
     "fbp.hip": ["-ffp-contract=off"],

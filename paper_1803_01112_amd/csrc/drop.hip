@@ -176,6 +176,12 @@ __device__ void tile_dots(const TileBlock &C, int64_t c0, int64_t c1, const Ent 
     }
 }
 
+// Dispatch slot of this workgroup.
+__device__ inline int64_t slot_of_wg(const DropTileArgs &A)
+{
+    return A.slots ? A.slots[blockIdx.x] : (int64_t)blockIdx.x;
+}
+
 __device__ inline void clear_next(const DropTileArgs &A, int nt)
 {
     if (!A.zero) return;
@@ -228,10 +234,11 @@ __global__ void __launch_bounds__(NT) k_drop_tile(DropTileArgs A)
 {
     __shared__ TileLds L;
     chain_priority();
-    const int64_t T = A.tiles[blockIdx.x];
+    const int64_t slot = slot_of_wg(A);
+    const int64_t T = A.tiles[slot];
     int64_t p0, p1, c0, c1;
-    list_range(A.P, blockIdx.x, p0, p1);
-    list_range(A.C, blockIdx.x, c0, c1);
+    list_range(A.P, slot, p0, p1);
+    list_range(A.C, slot, c0, c1);
     clear_next(A, NT);
     if (p0 == p1 && c0 == c1) return;
     double *xt = A.x + (T << kTileShift);
@@ -250,9 +257,10 @@ __global__ void __launch_bounds__(NT) k_drop_tile_finish(DropTileArgs A)
 {
     __shared__ TileLds L;
     chain_priority();
-    const int64_t T = A.tiles[blockIdx.x];
+    const int64_t slot = slot_of_wg(A);
+    const int64_t T = A.tiles[slot];
     int64_t p0, p1;
-    list_range(A.P, blockIdx.x, p0, p1);
+    list_range(A.P, slot, p0, p1);
     if (p0 == p1) return;
     double *xt = A.x + (T << kTileShift);
     const Ent pe = load_ent<CH>(A.P, p0 + threadIdx.x, p1);
@@ -268,9 +276,10 @@ __global__ void __launch_bounds__(NT) k_drop_tile_dots(DropTileArgs A)
 {
     __shared__ TileLds L;
     chain_priority();
-    const int64_t T = A.tiles[blockIdx.x];
+    const int64_t slot = slot_of_wg(A);
+    const int64_t T = A.tiles[slot];
     int64_t c0, c1;
-    list_range(A.C, blockIdx.x, c0, c1);
+    list_range(A.C, slot, c0, c1);
     clear_next(A, NT);
     if (c0 == c1) return;
     const double *xt = A.x + (T << kTileShift);

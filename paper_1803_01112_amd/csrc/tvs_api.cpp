@@ -41,6 +41,12 @@ constexpr int64_t kDevLogCap = 4096;
 // chain still reads the last two of this sweep.
 constexpr int kChunkBuffers = 3;
 
+// Blocks one launch of the resident chain takes at most (about 6 ms; a
+// launch's own cost is some 20 us).
+constexpr int64_t kChainBlocks = 1024;
+constexpr int kChainTable = 2048;            // slots of its row table
+constexpr int kChainLds = 160 * 1024 - 256;  // LDS of a CU it may take
+
 // Flags on the device: DROP fixed-point range, tile-list consistency,
 // history validation, longest vertex count, longest chord (float32 bits).
 enum {
@@ -202,12 +208,25 @@ struct tvs_ctx {
     std::vector<hipEvent_t> tev;
     size_t tev_used = 0;
     // kind: 0 TV steps, 1 sweep, 2 rows, 3 DROP, 4 first / 5 second launch of a sampled block
-    struct Span { int kind; size_t a, b; };
+    struct Span { int kind; size_t a, b; int64_t n; };   // n: blocks the span covers
     std::vector<Span> spans;
     bool timed = false;
     double last_sweep_ms = 0, last_tv_ms = 0, last_rows_ms = 0;
     double tot_ms[6] = {0, 0, 0, 0, 0, 0};
     int64_t tot_n[6] = {0, 0, 0, 0, 0, 0};
+
+    // the resident DROP chain (plan_chain); off when the grid or the block does not suit it
+    struct Chain {
+        bool on = false;
+        int nreg = 0, parts = 1, tmax = 0, ns = 0;
+        int32_t *reg = nullptr;     // nreg + 1: first slot of each region
+        int32_t *slots = nullptr;   // nact: slots by decreasing entries (launch per block)
+        uint32_t *bar = nullptr;    // barrier counters: all workgroups', then one per region
+        uint8_t *exch = nullptr;    // exchange records of the workgroups (parts > 1)
+        uint8_t *mem = nullptr;     // the allocation that holds them all
+        size_t bytes = 0;
+        uint32_t epoch = 0, sub_epoch = 0;
+    } chain;
 
     // batched reconstructions
     struct Batch {
@@ -245,11 +264,15 @@ int fail(tvs_ctx *ctx, int code, const std::string &msg)
             return fail(ctx, TVS_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
+void chain_release(tvs_ctx *ctx);
+
 template <typename T>
 int dalloc(tvs_ctx *ctx, T **p, size_t count)
 {
     size_t bytes = count * sizeof(T);
     if (bytes == 0) bytes = sizeof(T);
+    // the chain's small workspace gives way to whatever else needs the room
+    if (ctx->bytes + bytes > ctx->budget) chain_release(ctx);
     if (ctx->bytes + bytes > ctx->budget)
         return fail(ctx, TVS_ENOMEM,
                     "footprint " + std::to_string(ctx->bytes + bytes) + " B exceeds budget " +
@@ -277,6 +300,13 @@ void dfree(tvs_ctx *ctx, T **p, size_t count)
     }
 }
 
+void chain_release(tvs_ctx *ctx)
+{
+    auto &c = ctx->chain;
+    dfree(ctx, &c.mem, c.bytes);
+    c = tvs_ctx::Chain();
+}
+
 int64_t bt_len(const tvs_ctx *ctx) { return ctx->nblocks * ctx->nact + 1; }
 
 // Ring buffer of chunk c of the current sweep (on the fly).
@@ -295,6 +325,7 @@ void free_histories(tvs_ctx *ctx)
     ctx->mlp.nj = 0;
     dfree(ctx, &ctx->segtab, (size_t)ctx->nseg);
     dfree(ctx, &ctx->bt_off, (size_t)bt_len(ctx));
+    chain_release(ctx);
     dfree(ctx, &ctx->act, (size_t)std::max<int64_t>(ctx->nact, 1));
     dfree(ctx, &ctx->slot_of, (size_t)std::max<int64_t>(ctx->ntiles, 1));
     ctx->nact = 0;
@@ -414,9 +445,9 @@ long slot(tvs_ctx *ctx)
     return (long)ctx->tev_used++;
 }
 
-void span(tvs_ctx *ctx, int kind, long a, long b)
+void span(tvs_ctx *ctx, int kind, long a, long b, int64_t n = 1)
 {
-    if (a >= 0 && b >= 0) ctx->spans.push_back({kind, (size_t)a, (size_t)b});
+    if (a >= 0 && b >= 0) ctx->spans.push_back({kind, (size_t)a, (size_t)b, n});
 }
 
 // Pool events for the kernels of one sampled block, stamped by the launches
@@ -443,6 +474,11 @@ int check_flags(tvs_ctx *ctx, hipStream_t st)
     HIPCHK(hipStreamSynchronize(st));
     if (f[kFlagLists] || (f[kFlagRange] & 2u))
         return fail(ctx, TVS_EDEVICE, "a row walk disagreed with its load-time tile lists");
+    if (f[kFlagRange] & 4u) {
+        // the barrier's counters no longer match: launch block by block from here on
+        ctx->chain.on = false;
+        return fail(ctx, TVS_EDEVICE, "a workgroup of the DROP chain did not reach its barrier");
+    }
     if (f[kFlagRange])
         return fail(ctx, TVS_ERANGE,
                     "a DROP product |a_ij x_j| left the fixed-point range (image values too "
@@ -501,6 +537,92 @@ tvs::TileFill chunk_fill(tvs_ctx *ctx, int64_t c, int64_t n)
     return f;
 }
 
+// Blocks [b0, b1) of a sweep, one launch (or two) per block.
+int launch_blocks(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream_t st)
+{
+    const int64_t B = ctx->cfg.block_size;
+    HIPCHK(tvs::launch_zero_i64(ctx->dot, 3 * B, st));
+    for (int64_t b = b0; b <= b1; b++) {
+        const bool has_c = b < b1;
+        tvs::DropTileArgs A;
+        if (b > b0) A.P = block_view(ctx, b - 1, ctx->dot, B);
+        if (has_c) A.C = block_view(ctx, b, ctx->dot, B);
+        A.x = ctx->x;
+        A.lambda = lambda;
+        A.big = ctx->big;
+        A.dot_max = ctx->dot_max;
+        A.zero = ctx->dot + ((b + 1) % 3) * B;
+        A.B = B;
+        A.err = ctx->flags + kFlagRange;
+        A.tiles = ctx->act;
+        A.nact = ctx->nact;
+        A.slots = ctx->chain.slots;
+        const bool samp = ctx->cfg.time_sample > 0 && has_c && b > b0 &&
+                          b % ctx->cfg.time_sample == 0;
+        tvs::KTimer kt;
+        const bool timed = samp && ktimer(ctx, kt, ctx->split != 0);
+        HIPCHK(tvs::launch_drop_tiles(A, ctx->ntiles, ctx->threads, ctx->split, st,
+                                      timed ? &kt : nullptr));
+    }
+    return TVS_OK;
+}
+
+// Blocks [b0, b1) of a sweep by the resident chain; false: nothing was
+// launched (another process holds the device's cooperative queue), and the
+// blocks are to be launched one by one.
+bool run_chain(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream_t st)
+{
+    auto &c = ctx->chain;
+    const int64_t B = ctx->cfg.block_size;
+    const TileBlock v = block_view(ctx, b0, ctx->dot, B);
+    tvs::ChainArgs a;
+    a.meta = v.meta;
+    a.ch32 = v.ch32;
+    a.ch16 = v.ch16;
+    a.chq = v.chq;
+    a.qunit = v.qunit;
+    a.qshift = v.qshift;
+    a.rowmask = v.rowmask;
+    a.toff = ctx->bt_off;
+    a.nact = ctx->nact;
+    a.base = v.base;
+    a.act = ctx->act;
+    a.reg = c.reg;
+    a.wepl = ctx->hist + 12 * ctx->nh;
+    a.n2 = ctx->norm2;
+    a.dot = ctx->dot;
+    a.B = B;
+    a.nh = ctx->nh;
+    a.x = ctx->x;
+    a.cb = ctx->g;     // the subgradient is formed anew by every TV step
+    a.lambda = lambda;
+    a.big = ctx->big;
+    a.dot_max = ctx->dot_max;
+    a.err = ctx->flags + kFlagRange;
+    a.bar = c.bar;
+    a.sub = c.bar + tvs::kChainShards * 32;
+    a.exch = c.exch;
+    a.nreg = c.nreg;
+    a.parts = c.parts;
+    a.tmax = c.tmax;
+    a.ns = (uint32_t)c.ns;
+    a.wide = ctx->cfg.path_mode != TVS_PATH_ON_THE_FLY;
+    a.b0 = b0;
+    a.b1 = b1;
+    a.epoch = c.epoch;
+    a.sub_epoch = c.sub_epoch;
+    const bool timed = ctx->cfg.time_sample > 0;
+    const long e0 = timed ? mark(ctx, st) : -1;
+    if (tvs::launch_chain(a, st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (timed) span(ctx, 4, e0, mark(ctx, st), b1 - b0);
+    c.epoch += (uint32_t)(b1 - b0) + 1u;
+    c.sub_epoch += (uint32_t)(b1 - b0);
+    return true;
+}
+
 // One P_T sweep over the loaded histories (the first `limit` of them when
 // limit >= 0, a multiple of B: used to time launch shapes).
 int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
@@ -513,7 +635,10 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
     const int64_t step = otf ? ctx->chunk : ctx->nh;
     const int64_t nchunks = (nh_run + step - 1) / step;
     hipStream_t fs = ctx->fill_stream;
-    HIPCHK(tvs::launch_zero_i64(ctx->dot, 3 * B, st));
+    // a cooperative launch is not captured
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool chain = ctx->chain.on && hipStreamIsCapturing(st, &cap) == hipSuccess &&
+                       cap == hipStreamCaptureStatusNone;
     // a chunk is always formed whole, also when the sweep stops inside it:
     // its rows are formed in length order, so the first n of them are not
     // the histories of the first blocks
@@ -535,47 +660,31 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
         }
     }
     long e0 = mark(ctx, st);
-    for (int64_t b = 0; b <= nb; b++) {
-        const bool has_c = b < nb;
-        const int64_t c = has_c ? (b * B) / step : -1;
-        const bool first_of_chunk = has_c && (b * B) % step == 0;
-        if (otf && first_of_chunk)
-            HIPCHK(hipStreamWaitEvent(st, ctx->ev_filled[chunk_buffer(ctx, c)], 0));
-        tvs::DropTileArgs A;
-        if (b > 0) A.P = block_view(ctx, b - 1, ctx->dot, B);
-        if (has_c) A.C = block_view(ctx, b, ctx->dot, B);
-        A.x = ctx->x;
-        A.lambda = lambda;
-        A.big = ctx->big;
-        A.dot_max = ctx->dot_max;
-        A.zero = ctx->dot + ((b + 1) % 3) * B;
-        A.B = B;
-        A.err = ctx->flags + kFlagRange;
-        A.tiles = ctx->act;
-        A.nact = ctx->nact;
-        const bool samp = ctx->cfg.time_sample > 0 && has_c && b > 0 &&
-                          b % ctx->cfg.time_sample == 0;
-        tvs::KTimer kt;
-        const bool timed = samp && ktimer(ctx, kt, ctx->split != 0);
-        HIPCHK(tvs::launch_drop_tiles(A, ctx->ntiles, ctx->threads, ctx->split, st,
-                                      timed ? &kt : nullptr));
-        if (otf && first_of_chunk && c >= 1) {
-            // the launch above was the last to read chunk c - 1's buffer,
-            // which takes chunk c - 1 + NB next
-            HIPCHK(hipEventRecord(ctx->ev_free[chunk_buffer(ctx, c - 1)], st));
-            if (c - 1 + NB < nchunks) {
-                int rc = fill(c - 1 + NB);
+    for (int64_t c = 0; c < nchunks; c++) {
+        const int64_t c0 = c * step / B, c1 = std::min(nb, ((c + 1) * step + B - 1) / B);
+        if (otf) HIPCHK(hipStreamWaitEvent(st, ctx->ev_filled[chunk_buffer(ctx, c)], 0));
+        // at most kChainBlocks blocks a launch, so that reconstructions on
+        // other streams, whose chains wait for this one, get their turn
+        for (int64_t b = c0; b < c1;) {
+            const int64_t e = chain ? std::min(c1, b + kChainBlocks) : c1;
+            if (!chain || !run_chain(ctx, lambda, b, e, st)) {
+                int rc = launch_blocks(ctx, lambda, b, e, st);
+                if (rc) return rc;
+            }
+            b = e;
+        }
+        if (otf) {
+            HIPCHK(hipEventRecord(ctx->ev_free[chunk_buffer(ctx, c)], st));
+            if (c + NB < nchunks) {
+                int rc = fill(c + NB);
                 if (rc) return rc;
             }
         }
     }
     span(ctx, 3, e0, mark(ctx, st));
-    if (otf) {
-        HIPCHK(hipEventRecord(ctx->ev_free[chunk_buffer(ctx, nchunks - 1)], st));
-        // the ring continues with the next sweep, whose first chunks take the
-        // buffers freed first
-        ctx->cbase = (ctx->cbase + nchunks) % NB;
-    }
+    // the ring continues with the next sweep, whose first chunks take the
+    // buffers freed first
+    if (otf) ctx->cbase = (ctx->cbase + nchunks) % NB;
     return TVS_OK;
 }
 
@@ -616,6 +725,125 @@ int count_rows(tvs_ctx *ctx, int64_t first, int64_t n, int64_t *row_off_dev, hip
     return TVS_OK;
 }
 
+// Places the active tiles in regions of the resident chain (chain.hip), one
+// region per workgroup: reorders a (the tiles by slot) and fills reg, the
+// first slot of each region.  False where the chain does not fit: explicit
+// launch shapes, blocks of more rows than a packed entry names, images whose
+// crossed tiles do not fit the device's LDS.
+bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<int32_t> &a,
+                std::vector<int32_t> &reg)
+{
+    auto &c = ctx->chain;
+    const int64_t B = ctx->cfg.block_size;
+    if (ctx->cfg.sweep_kernel != 0 || ctx->cfg.tile_threads != 0 || B > tvs::kChainMaxB) return false;
+    int cus = 0, coop = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->cfg.device) != hipSuccess ||
+        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, ctx->cfg.device) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (!coop || cus < 1) return false;
+    // Beside the row formation of several chunks the chain's workgroups and
+    // the row kernel's do not fit a CU together (200x200x16 on the fly: 15.6 ms
+    // a cycle against 14.2 launched block by block), so rows formed on the fly
+    // take it only when one chunk holds them all.
+    if (ctx->cfg.path_mode == TVS_PATH_ON_THE_FLY && ctx->nh > ctx->chunk) return false;
+    const int n = (int)a.size();
+    // Many tiles and long lists: a launch's workgroups fill the device, and
+    // the chain's one workgroup per CU is bound by instruction issue (256x256x32
+    // at B = 25,600, 20,000 entries a CU: 44 us a block against 42 launched).
+    // Shorter lists or fewer tiles are the chain's (2,000 entries a CU: 7.2
+    // against 8.8 us).
+    const double avg = (double)ctx->nnz / (double)std::max<int64_t>(ctx->nblocks, 1);
+    if (n >= 4 * cus && avg > 8192.0 * cus) return false;
+    c.ns = kChainTable;
+    int cap = tvs::kChainMaxTiles;
+    while (cap > 0 && tvs::chain_lds_bytes(cap, c.ns) > (size_t)kChainLds) cap--;
+    if (cap < 1 || (int64_t)cap * cus < n) return false;
+    // neighbours in a slice next to each other (Morton order of the tiles), so
+    // that a row crosses few regions
+    const GridDev &g = ctx->gd;
+    auto key = [&](int32_t T) {
+        const int64_t z = T / ((int64_t)g.ntx * g.nty);
+        const uint32_t i = (uint32_t)(T % g.ntx), j = (uint32_t)((T / g.ntx) % g.nty);
+        uint64_t m = 0;
+        for (int q = 0; q < 16; q++)
+            m |= (uint64_t)(((i >> q) & 1u) | (((j >> q) & 1u) << 1)) << (2 * q);
+        return ((uint64_t)z << 32) | m;
+    };
+    std::sort(a.begin(), a.end(), [&](int32_t x, int32_t y) { return key(x) < key(y); });
+    // a tile's work per block: its entries, and its words (a quarter of an entry each)
+    const double nb = (double)std::max<int64_t>(ctx->nblocks, 1);
+    double total = 0.0, most = 0.0;
+    std::vector<double> w(a.size());
+    for (size_t i = 0; i < a.size(); i++) {
+        w[i] = (double)entries[(size_t)a[i]] / nb + 64.0;
+        total += w[i];
+        most = std::max(most, w[i]);
+    }
+    auto cut = [&](double limit) {
+        reg.assign(1, 0);
+        double sum = 0.0;
+        for (int i = 0; i < n; i++) {
+            if (i > reg.back() && (sum + w[(size_t)i] > limit || i - reg.back() >= cap)) {
+                reg.push_back(i);
+                sum = 0.0;
+            }
+            sum += w[(size_t)i];
+        }
+        reg.push_back(n);
+        return (int)reg.size() - 1;
+    };
+    if (n <= cus) {
+        for (int i = 0; i <= n; i++) reg.push_back(i);
+        // few tiles: several workgroups per tile, as far as the busiest
+        // tile's list of a block fills them
+        const double per = 2.0 * tvs::kChainThreads;
+        c.parts = std::max(1, std::min(std::min(cus / n, 32), (int)std::ceil((most - 64.0) / per)));
+    } else {
+        double lo = std::max(most, total / cus), hi = total + 1.0;
+        if (cut(hi) > cus) return false;       // the tile cap alone needs more regions
+        for (int q = 0; q < 40; q++) {
+            const double mid = 0.5 * (lo + hi);
+            if (cut(mid) <= cus) hi = mid;
+            else lo = mid;
+        }
+        cut(hi);
+        c.parts = 1;
+    }
+    c.nreg = (int)reg.size() - 1;
+    c.tmax = 0;
+    for (int r = 0; r < c.nreg; r++) c.tmax = std::max(c.tmax, reg[(size_t)r + 1] - reg[(size_t)r]);
+    return true;
+}
+
+// The chain's device data; without room for it the chain stays off.
+int chain_upload(tvs_ctx *ctx, const std::vector<int32_t> &reg, const std::vector<int32_t> &slots,
+                 hipStream_t st)
+{
+    auto &c = ctx->chain;
+    // one allocation: counters and exchange records (cleared), then the tables
+    const size_t nbar = 4 * (size_t)(tvs::kChainShards + c.nreg) * 32;
+    const size_t nexch = c.parts > 1 ? (size_t)c.nreg * c.parts * tvs::kChainExchBytes : 0;
+    std::vector<int32_t> tab(reg);
+    tab.insert(tab.end(), slots.begin(), slots.end());
+    c.bytes = nbar + nexch + 4 * tab.size();
+    if (ctx->bytes + c.bytes > ctx->budget || dalloc(ctx, &c.mem, c.bytes)) {
+        ctx->err.clear();
+        chain_release(ctx);
+        return TVS_OK;
+    }
+    c.bar = reinterpret_cast<uint32_t *>(c.mem);
+    c.exch = c.mem + nbar;
+    c.reg = reinterpret_cast<int32_t *>(c.mem + nbar + nexch);
+    c.slots = c.reg + reg.size();
+    HIPCHK(hipMemsetAsync(c.mem, 0, nbar + nexch, st));
+    HIPCHK(hipMemcpyAsync(c.reg, tab.data(), 4 * tab.size(), hipMemcpyHostToDevice, st));
+    HIPCHK(hipStreamSynchronize(st));
+    c.on = true;
+    return TVS_OK;
+}
+
 // The tiles that some block's lists cross (a tile outside the scanned
 // object has no entry in any block), from the (block, tile) list lengths:
 // the DROP steps launch one workgroup per such tile only, in order of
@@ -641,15 +869,25 @@ int build_active_tiles(tvs_ctx *ctx, const uint32_t *btc, hipStream_t st)
     std::vector<int32_t> a;
     for (int64_t T = 0; T < nt; T++)
         if (f[(size_t)T]) a.push_back((int32_t)T);
-    std::stable_sort(a.begin(), a.end(),
-                     [&](int32_t x, int32_t y) { return f[(size_t)x] > f[(size_t)y]; });
+    auto busier = [&](int32_t x, int32_t y) { return f[(size_t)x] > f[(size_t)y]; };
+    std::stable_sort(a.begin(), a.end(), busier);
     if (a.empty()) a.push_back(0);
+    ctx->nact = (int64_t)a.size();
+    std::vector<int32_t> reg, busiest, placed = a;
+    if (plan_chain(ctx, f, placed, reg)) {
+        a.swap(placed);
+        busiest.resize(a.size());
+        for (size_t i = 0; i < a.size(); i++) busiest[i] = (int32_t)i;
+        std::stable_sort(busiest.begin(), busiest.end(),
+                         [&](int32_t x, int32_t y) { return busier(a[(size_t)x], a[(size_t)y]); });
+        rc = chain_upload(ctx, reg, busiest, st);
+        if (rc) return rc;
+    }
     std::vector<int32_t> inv((size_t)std::max<int64_t>(nt, 1), -1);
     for (size_t i = 0; i < a.size(); i++) inv[(size_t)a[i]] = (int32_t)i;
     rc = dalloc(ctx, &ctx->act, a.size());
     if (!rc) rc = dalloc(ctx, &ctx->slot_of, inv.size());
     if (rc) return rc;
-    ctx->nact = (int64_t)a.size();
     e = hipMemcpyAsync(ctx->act, a.data(), sizeof(int32_t) * a.size(), hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(ctx->slot_of, inv.data(), sizeof(int32_t) * inv.size(),
@@ -1584,7 +1822,7 @@ int tvs_get_stats(tvs_ctx *ctx, tvs_stats *out)
             float ms = 0;
             HIPCHK(hipEventElapsedTime(&ms, ctx->tev[sp.a], ctx->tev[sp.b]));
             ctx->tot_ms[sp.kind] += ms;
-            ctx->tot_n[sp.kind] += 1;
+            ctx->tot_n[sp.kind] += sp.n;
             if (sp.kind == 0) {
                 last_cycle_start = sp.a;
                 last[0] = ms;
@@ -1831,6 +2069,7 @@ int batch_cycle(tvs_ctx *ctx, int nmax, hipStream_t st)
         A.err = ctx->flags + kFlagRange;
         A.tiles = ctx->act;
         A.nact = ctx->nact;
+        A.slots = ctx->chain.slots;
         HIPCHK(tvs::launch_drop_tiles_batch(A, Bt.b, ctx->ntiles, ctx->bthreads, ctx->bgroup, st));
         if (otf && first_of_chunk && c >= 1 && c - 1 + NB < nchunks) {
             // the launch above was the last to read chunk c - 1's buffer
@@ -2061,6 +2300,9 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
     HIPCHK(hipMemcpyAsync(saved, ctx->x, sizeof(double) * ctx->nvox, hipMemcpyDeviceToDevice, st));
     const int ths[3] = {64, 128, 256};
     const int old_threads = ctx->threads, old_split = ctx->split;
+    // the candidates are launches per block; the chain goes on where it fits
+    const bool chain = ctx->chain.on;
+    ctx->chain.on = false;
     double best = 1e300;
     int nc = 0;
     for (int sw = 1; sw <= 2 && rc == TVS_OK; sw++) {
@@ -2104,6 +2346,7 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
         }
     }
     out->n_candidates = nc;
+    ctx->chain.on = chain && ctx->chain.reg;
     if (rc || best == 1e300) {
         dfree(ctx, &saved, (size_t)ctx->nvox);
         ctx->tev_used = 0;
@@ -2247,6 +2490,7 @@ int tvs_autotune_batch(tvs_ctx *ctx, const tvs_params *p, int32_t S, const char 
                     A.err = ctx->flags + kFlagRange;
                     A.tiles = ctx->act;
                     A.nact = ctx->nact;
+                    A.slots = ctx->chain.slots;
                     e = tvs::launch_drop_tiles_batch(A, Bt.b, ctx->ntiles, ctx->bthreads,
                                                      ctx->bgroup, st);
                 }

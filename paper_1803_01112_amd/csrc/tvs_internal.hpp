@@ -255,6 +255,9 @@ struct DropTileArgs {
     // nact workgroups
     const int32_t *tiles = nullptr;
     int64_t nact = 0;
+    // dispatch order of the slots (busiest first) where the slots themselves
+    // are laid out by region; null: slot order
+    const int32_t *slots = nullptr;
 };
 
 // Start/stop events of the kernels of one block (first and second launch);
@@ -275,6 +278,49 @@ hipError_t launch_slot_counts(const uint32_t *cnt, const int32_t *act, int64_t n
                               int64_t nblocks, int64_t ntiles, uint32_t *out, hipStream_t stream);
 hipError_t launch_tile_totals(const uint32_t *cnt, int64_t nblocks, int64_t ntiles,
                               uint32_t *total, hipStream_t stream);
+
+// ----------------------------------------------------------------- chain.hip
+// The DROP chain of many blocks as one resident kernel: nreg regions of
+// consecutive dispatch slots (at most tmax image tiles each), `parts`
+// workgroups per region (more than one only when every region is one tile).
+constexpr int kChainThreads = 512;
+constexpr int kChainShards = 16;          // counters of the device-wide barrier, 32 words apart
+constexpr int kChainMaxTiles = 32;        // tiles of a region (5 bits of a packed entry)
+constexpr int64_t kChainMaxB = (1 << 18) - 1;   // rows of a block (18 bits of a packed entry)
+constexpr size_t kChainExchBytes = 8192;  // exchange record of one workgroup
+struct ChainArgs {
+    const uint32_t *meta = nullptr;   // entry e (global index) at meta[e - base]
+    const float *ch32 = nullptr;
+    const __half *ch16 = nullptr;
+    const uint16_t *chq = nullptr;
+    double qunit = 0.0;
+    uint32_t qshift = 31, rowmask = 0xffffffu;
+    const int64_t *toff = nullptr;    // list starts by (block, slot)
+    int64_t nact = 0, base = 0;
+    const int32_t *act = nullptr;     // slot -> tile
+    const int32_t *reg = nullptr;     // nreg + 1: first slot of each region
+    const float *wepl = nullptr, *n2 = nullptr;   // per history
+    long long *dot = nullptr;         // 3 x B fixed-point row dot products
+    int64_t B = 0, nh = 0;
+    int64_t b0 = 0, b1 = 0;           // blocks [b0, b1), each one finished in this launch
+    double *x = nullptr;
+    double *cb = nullptr;             // scratch image: float64 sums of large corrections
+    double lambda = 0.0, big = 0.0, dot_max = 0.0;
+    double corr_small = 0.0, dot_small = 0.0;   // set by launch_chain: ranges of the short rounding
+    uint32_t *err = nullptr;          // bits 0 and 1 as in DropTileArgs, bit 2: a wait timed out
+    uint32_t *bar = nullptr;          // barrier counters (kChainShards x 32 words), only counted up
+    uint32_t *sub = nullptr;          // nreg x 32 words: a region's own barrier (parts > 1)
+    uint32_t epoch = 0, sub_epoch = 0;   // barriers passed before this launch
+    void *exch = nullptr;             // nreg * parts exchange records (parts > 1)
+    int32_t nreg = 0, parts = 1, tmax = 0;
+    uint32_t ns = 0;                  // slots of the row table (a power of two)
+    int32_t wide = 0;                 // 1: 1,024 lanes a workgroup, else 512
+};
+size_t chain_lds_bytes(int tmax, int ns);
+// An error leaves everything as it was (for instance a device whose
+// cooperative queue another process holds): the caller launches the blocks
+// one by one instead.
+hipError_t launch_chain(const ChainArgs &a, hipStream_t stream);
 
 // ----------------------------------------------------------------- tv.hip
 struct TvBuffers {
