@@ -23,6 +23,7 @@ struct GridDev {
     double ox, oy, oz;
     int32_t ntx, nty;         // tiles per slice along x and y
     double rvx, rvy, rvz;     // 1/vx, 1/vy, 1/vz rounded to nearest
+    bool short_ok;            // at most 4,096 voxels per axis (rows.hip's short segments)
 };
 
 // Tiled layout.  Each slice is cut into 16 x 16 voxel tiles of 256
@@ -79,7 +80,8 @@ inline GridDev make_grid_dev(const tvs_grid &g)
 {
     return GridDev{g.nx, g.ny, g.nz, g.vx, g.vy, g.vz, g.ox, g.oy, g.oz,
                    (g.nx + kTileSide - 1) / kTileSide, (g.ny + kTileSide - 1) / kTileSide,
-                   1.0 / g.vx, 1.0 / g.vy, 1.0 / g.vz};
+                   1.0 / g.vx, 1.0 / g.vy, 1.0 / g.vz,
+                   g.nx <= 4096 && g.ny <= 4096 && g.nz <= 4096};
 }
 
 // SoA history streams on the device: 13 float32 arrays of length n, one

@@ -1,0 +1,83 @@
+"""Rows at the edges of the short-segment walk: its voxels must be the general
+walk's, bit for bit those of the oracle, wherever a segment is short only by
+a hair or not at all.  Lines along axes and diagonals on and next to grid
+planes and edges, through corners, entering, leaving and missing the grid;
+vertex spacings from a fifth of a voxel to several voxels; curved paths in
+random directions; one voxel, one slice, and the last partly filled
+wavefront."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1803_01112_amd import synth, tvs
+
+pytestmark = pytest.mark.gpu
+
+
+def check(grid, h, step, mode="f32"):
+    n = len(h["ex"])
+    print(f"rows {tuple(grid[:3])} step {step} n {n}", flush=True)
+    rows = oracle.build_rows(grid, h, step)
+    with tvs.Context(grid, block_size=97, mlp_step_mm=step, path_mode=mode) as ctx:
+        ctx.load_histories(h)
+        rn, idx, ch, n2 = ctx.debug_rows(0, n)
+        x0 = np.linspace(0.5, 1.5, grid.nvox).astype(np.float32)
+        ctx.set_image(x0)
+        ctx.iterate(1, 0.05, 0, 0.75)
+        try:
+            x = ctx.get_image()
+        except tvs.TvsError as e:
+            assert e.status == tvs.TVS_ERANGE
+            x = None
+    np.testing.assert_array_equal(rn, np.diff(rows["row_off"]))
+    np.testing.assert_array_equal(idx, rows["idx"])
+    ref = rows["chord"]
+    assert np.all(np.abs(ch.astype(np.float64) - ref) <= np.spacing(np.abs(ref).astype(np.float32)))
+    S = oracle.Superiorizer(grid, rows, x0, 97)      # the tile lists hold the same rows
+    S.iterate(1, 0.05, 0, 0.75, seed=0)
+    if x is None:                                    # rows of hairs drive the image out of range
+        assert np.max(np.abs(S.x)) * np.max(ref) > 2.0 ** 26 / max(np.max(rn), 1)
+        return
+    assert np.max(np.abs(x - S.x) / np.maximum(np.abs(S.x), 0.1)) <= 1e-4
+
+
+def lines(grid, n, seed):
+    """Straight lines between points on a lattice of planes, edges and voxel
+    centres (and a hair off them), inside and outside the grid."""
+    rng = np.random.default_rng(seed)
+    lo = np.array([grid.ox, grid.oy, grid.oz])
+    v = np.array([grid.vx, grid.vy, grid.vz])
+    dim = np.array(grid[:3])
+
+    def points():
+        k = rng.integers(-2, dim * 2 + 3, (n, 3)) * 0.5
+        k = k + rng.choice([0.0, 0.0, 1e-7, -1e-7, 1e-5, -1e-5, 0.013], (n, 3))
+        return lo + v * k
+    p, q = points(), points()
+    axis = rng.integers(0, 3, n)                   # a third along x, a third along y
+    q[axis == 0, 1:] = p[axis == 0, 1:]
+    q[axis == 1, 0] = p[axis == 1, 0]
+    same = np.all(np.abs(p[:, :2] - q[:, :2]) < 1e-6, axis=1)
+    q[same, 0] += 3.0
+    return synth.line_histories(p, q, rng.uniform(1.0, 50.0, n))
+
+
+@pytest.mark.parametrize("dims,vox", [((17, 16, 3), (1.0, 1.0, 2.5)), ((1, 1, 1), (2.0, 2.0, 2.0)),
+                                      ((33, 5, 1), (1.3, 0.7, 2.0)), ((64, 64, 2), (1.0, 1.0, 1.0))])
+@pytest.mark.parametrize("step", [0.2, 1.0, 5.3])
+def test_rows_of_lines_on_planes(dims, vox, step):
+    grid = synth.centered_grid(*dims, *vox)
+    check(grid, lines(grid, 1003, int(step * 10) + dims[0]), step)
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 257])
+def test_rows_of_curved_paths(n):
+    """Bent paths (exit slopes up to 1) in random directions, both ends in or
+    near the grid."""
+    grid = synth.centered_grid(40, 28, 6, 1.0, 1.0, 2.5)
+    rng = np.random.default_rng(n)
+    h = lines(grid, n, n)
+    for k in ("eth", "eps", "qth", "qps"):
+        h[k] = rng.uniform(-1.0, 1.0, n).astype(np.float32)
+    for step in (0.3, 1.0):
+        check(grid, h, step, "otf")
