@@ -14,6 +14,7 @@
 // Decisions that pick voxel indices are taken in float64; chords are
 // rounded to float32 (or float16) only when written.  This file must be
 // compiled with -ffp-contract=off so that no multiply-add is fused.
+#include <algorithm>
 #include <type_traits>
 
 #include "tvs_internal.hpp"
@@ -182,8 +183,7 @@ __device__ inline void mvec(const M2 &A, double x0, double x1, double &y0, doubl
 //   kSeg      reserves each segment's place in its (block, tile) list;
 //   kRowMajor writes the entries in walk order (tvs_debug_rows);
 //   kTiled    writes every entry into its tile list at the reserved place.
-//   kHull     counts each voxel of a straight line once in in_cnt / out_cnt.
-enum EmitMode { kCount = 0, kSeg = 1, kRowMajor = 2, kTiled = 3, kHull = 4 };
+enum EmitMode { kCount = 0, kSeg = 1, kRowMajor = 2, kTiled = 3 };
 
 // A chord as an unsigned multiple of the fixed-point store's unit (1 / qinv
 // mm), rounded to nearest; the unit is the longest chord of the loaded rows
@@ -209,10 +209,6 @@ struct Emit {
     uint32_t qmax = 0;           // kTiled, fixed-point chords: largest code
     uint32_t qshift = 31;        // kTiled, fixed-point chords: tag bit of the code's bit 16
     double maxc = 0.0;           // kSeg: longest entry of the row
-    uint32_t *in_cnt = nullptr;  // kHull: this line counts (space modelling) into in_cnt,
-    uint32_t *out_cnt = nullptr; //        carves (space carving) into out_cnt,
-    uint32_t in_sat = 0;         //        each count only up to the value past which no
-    uint32_t out_sat = 0;        //        further line changes the voxel's decision
     uint32_t *btc = nullptr;     // kSeg: list lengths of this row's block
     uint64_t *segtab = nullptr;  // kSeg: (tile, place) of this row's segments
     const int64_t *segdst = nullptr;  // kTiled: first entry of this row's segments
@@ -255,21 +251,6 @@ struct Emit {
     __device__ inline void flush()
     {
         if (cur < 0) return;
-        if constexpr (MODE == kHull) {
-            // a count read below its true value (another line's add not yet
-            // seen) only costs an add; one at or past the saturation value
-            // has reached it for good (counts only grow)
-            if (in_cnt && __hip_atomic_load(in_cnt + cur, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT) < in_sat)
-                atomicAdd(in_cnt + cur, 1u);
-            if (out_cnt && __hip_atomic_load(out_cnt + cur, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT) < out_sat)
-                atomicAdd(out_cnt + cur, 1u);
-            cur = -1;
-            cur_len = 0.0;
-            n++;
-            return;
-        }
         const int32_t t = cur >> kTileShift;
         if (t != tile) {
             close_seg();
@@ -903,33 +884,163 @@ k_validate(HistDev H, int64_t n, double step, uint32_t *bad, uint32_t *jmax)
 }
 
 // Hull detection: every history's straight line from its entry to its exit
-// point, walked like a row segment; a line whose WEPL reaches wepl_in counts
-// its voxels (space modelling), one whose WEPL is below wepl_out carves them
-// (space carving).  One lane per history; the counters are in the tiled
-// layout and saturate at in_sat / out_sat (min_in and max_out + 1): past
-// them no further line changes a decision, and most adds are skipped.
-__global__ void __launch_bounds__(kThreads)
-k_hull_counts(GridDev g, HistDev H, int64_t n, double wepl_in, double wepl_out, uint32_t *in_cnt,
-              uint32_t *out_cnt, uint32_t in_sat, uint32_t out_sat)
+// point; a line whose WEPL reaches wepl_in counts its voxels (space
+// modelling), one whose WEPL is below wepl_out carves them (space carving).
+// One lane per history; the counters (x-fastest) saturate at in_sat / out_sat
+// (min_in and max_out + 1): past them no further line changes a decision, and
+// most adds are skipped.  A count read below its true value (another line's
+// add not yet seen) only costs an add; one at the value has reached it for
+// good.
+struct HullCounts {
+    uint32_t *in_cnt, *out_cnt;
+    const uint32_t *in_full, *out_full;   // voxels at their value, a bit each (may be null)
+    uint32_t in_sat, out_sat;
+};
+
+__device__ inline uint32_t hull_word(const uint32_t *full, int32_t p) { return full ? full[p >> 5] : 0u; }
+
+// Counts voxel p; word: the full-voxel bits that hold it.
+__device__ inline void hull_count(uint32_t *cnt, uint32_t word, uint32_t sat, int32_t p)
 {
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if ((word >> (p & 31)) & 1u) return;
+    if (__hip_atomic_load(cnt + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < sat)
+        atomicAdd(cnt + p, 1u);
+}
+
+// The line g0 -> g1 (grid coordinates): the pieces of walk_segment.  While
+// crossings are apart by more than eps of the line, their order follows from
+// parameters stepped by 1 / |dg| (rounding far below eps), and a piece's
+// voxel from the planes crossed so far: its midpoint keeps half the piece
+// times the slowest crossing axis' |dg| (1e-8) from every plane that axis
+// crosses, and kClear from the others.  Where two parameters come within eps
+// of each other or of the end, they are formed as walk_segment forms them,
+// and a piece no longer than eps takes its voxel at the midpoint; a line that
+// touches a plane without crossing it does so all the way.
+__device__ inline void hull_line(const GridDev &g, const double g0[3], const double g1[3],
+                                 const HullCounts &h, bool in, bool out)
+{
+    const int32_t n[3] = {g.nx, g.ny, g.nz};
+    const int32_t stride[3] = {1, g.nx, g.nx * g.ny};
+    double t[3], dt[3], slow = 1.0;
+    int32_t c[3], dir[3], p = 0, last = -1;
+    bool loose = !g.short_ok;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        const double dg = g1[a] - g0[a];
+        const double lo = g0[a] < g1[a] ? g0[a] : g1[a], hi = g0[a] < g1[a] ? g1[a] : g0[a];
+        const double top = (double)n[a], fl = floor(lo);
+        double mlo = fl + 1.0, mhi = ceil(hi) - 1.0;
+        if (mlo < 0.0) mlo = 0.0;
+        if (mhi > top) mhi = top;
+        t[a] = 2.0;
+        dt[a] = 0.0;
+        dir[a] = 0;
+        if (dg != 0.0 && mlo <= mhi) {
+            dir[a] = dg > 0.0 ? 1 : -1;
+            c[a] = dg > 0.0 ? (int32_t)mlo - 1 : (int32_t)mhi;
+            t[a] = ((dg > 0.0 ? mlo : mhi) - g0[a]) / dg;
+            dt[a] = fabs(1.0 / dg);
+            slow = fabs(dg) < slow ? fabs(dg) : slow;
+        } else {
+            c[a] = hi < 0.0 ? -1 : lo > top ? n[a] : (int32_t)fl;
+            const bool off = hi < -kClear || lo > top + kClear;
+            loose = loose || (dg != 0.0 && !off && !(lo - fl > kClear && hi - fl < 1.0 - kClear));
+        }
+        p += c[a] * stride[a];
+    }
+    const double eps = loose ? 4.0 : 2.0e-8 / slow;
+    double prev = 0.0;
+    // a voxel is counted one piece later: its bits arrive meanwhile
+    uint32_t win = 0u, wout = 0u;
+    auto count_last = [&]() {
+        if (last < 0) return;
+        if (in) hull_count(h.in_cnt, win, h.in_sat, last);
+        if (out) hull_count(h.out_cnt, wout, h.out_sat, last);
+    };
+    for (;;) {
+        const double lo = fmin(t[0], t[1]), hi = fmax(t[0], t[1]);
+        double tb = fmin(lo, t[2]);
+        const double second = fmin(fmin(hi, fmax(lo, t[2])), 1.0);
+        bool inside = (uint32_t)c[0] < (uint32_t)n[0] && (uint32_t)c[1] < (uint32_t)n[1] &&
+                      (uint32_t)c[2] < (uint32_t)n[2];
+        int32_t at = p;
+        if (second - tb < eps) {
+#pragma unroll
+            for (int a = 0; a < 3; a++) {
+                // the plane ahead; past the grid's planes there is none
+                const int32_t m = c[a] + (dir[a] > 0 ? 1 : 0);
+                if (dir[a])
+                    t[a] = (m >= 0 && m <= n[a]) ? ((double)m - g0[a]) / (g1[a] - g0[a]) : 2.0;
+            }
+            tb = fmin(fmin(t[0], t[1]), fmin(t[2], 1.0));
+            if (!(tb - prev > eps)) {
+                const double tm = (prev + tb) * 0.5;
+                inside = tb > prev;
+                at = 0;
+#pragma unroll
+                for (int a = 0; a < 3; a++) {
+                    const double f = floor(g0[a] + tm * (g1[a] - g0[a]));
+                    inside = inside && !(f < 0.0 || f >= (double)n[a]);
+                    at += (inside ? (int32_t)f : 0) * stride[a];
+                }
+            }
+        }
+        if (inside && at != last) {
+            count_last();
+            last = at;
+            win = in ? hull_word(h.in_full, at) : 0u;
+            wout = out ? hull_word(h.out_full, at) : 0u;
+        }
+        prev = tb;
+        bool more = tb < 1.0;
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            const bool cross = t[a] == tb;
+            t[a] += cross ? dt[a] : 0.0;
+            c[a] += cross ? dir[a] : 0;
+            p += cross ? (dir[a] > 0 ? stride[a] : -stride[a]) : 0;
+            // out by the last plane of this axis: nothing more inside
+            more = more && (loose || !cross || (uint32_t)c[a] < (uint32_t)n[a] ||
+                            (dir[a] > 0 ? c[a] < 0 : c[a] >= n[a]));
+        }
+        if (!more) break;
+    }
+    count_last();
+}
+
+__global__ void __launch_bounds__(kThreads)
+k_hull_counts(GridDev g, HistDev H, int64_t first, int64_t n, double wepl_in, double wepl_out,
+              HullCounts h)
+{
+    const int64_t i = first + (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= n) return;
     const double w = H.s(kWepl)[i];
-    const bool in = w >= wepl_in, out = w < wepl_out;
+    const bool in = w >= wepl_in && h.in_sat > 0u, out = w < wepl_out;
     if (!in && !out) return;
     const double p0[3] = {H.s(kEx)[i], H.s(kEy)[i], H.s(kEz)[i]};
     const double p1[3] = {H.s(kQx)[i], H.s(kQy)[i], H.s(kQz)[i]};
+    const double dx = p1[0] - p0[0], dy = p1[1] - p0[1], dz = p1[2] - p0[2];
+    if (!(dx * dx + dy * dy + dz * dz > 0.0)) return;
     double g0[3], g1[3];
     to_grid(g, p0, g0);
     to_grid(g, p1, g1);
-    Emit<kHull, float> e;
-    e.in_cnt = in ? in_cnt : nullptr;
-    e.out_cnt = out ? out_cnt : nullptr;
-    e.in_sat = in_sat;
-    e.out_sat = out_sat;
-    const double dx = p1[0] - p0[0], dy = p1[1] - p0[1], dz = p1[2] - p0[2];
-    walk_segment<kHull, float>(g, sqrt(dx * dx + dy * dy + dz * dz), g0, g1, e);
-    e.flush();
+    hull_line(g, g0, g1, h, in, out);
+}
+
+// A bit per voxel: its count has reached sat (in words [0, nw), out after them).
+__global__ void __launch_bounds__(kThreads)
+k_hull_full(const uint32_t *in_cnt, const uint32_t *out_cnt, int64_t n, uint32_t in_sat,
+            uint32_t out_sat, uint32_t *full, int64_t nw)
+{
+    const int64_t q = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const uint64_t bi = __ballot(q < n && in_cnt[q < n ? q : 0] >= in_sat);
+    const uint64_t bo = __ballot(q < n && out_cnt[q < n ? q : 0] >= out_sat);
+    const int lane = threadIdx.x & 63;
+    const int64_t w = (q >> 6) * 2 + (lane & 1);
+    if (lane < 2 && w < nw) {
+        full[w] = (uint32_t)(bi >> (32 * lane));
+        full[nw + w] = (uint32_t)(bo >> (32 * lane));
+    }
 }
 
 // hull[p] (x-fastest) = in_cnt >= min_in and out_cnt <= max_out; with mask,
@@ -943,7 +1054,7 @@ k_hull_decide(GridDev g, const uint32_t *in_cnt, const uint32_t *out_cnt, uint32
          p += (int64_t)gridDim.x * kThreads) {
         const int64_t ii = p % g.nx, t = p / g.nx, jj = t % g.ny, kk = t / g.ny;
         const int64_t a = vaddr(g, ii, jj, kk);
-        const bool inside = in_cnt[a] >= min_in && out_cnt[a] <= max_out;
+        const bool inside = in_cnt[p] >= min_in && out_cnt[p] <= max_out;
         hull[p] = inside ? 1u : 0u;
         if (mask && !inside) mask[a] = 0.0;
     }
@@ -1115,12 +1226,35 @@ hipError_t launch_validate(const HistDev &h, int64_t n, double step, uint32_t *b
 
 hipError_t launch_hull_counts(const GridDev &g, const HistDev &h, int64_t n, double wepl_in,
                               double wepl_out, uint32_t *in_cnt, uint32_t *out_cnt,
-                              uint32_t in_sat, uint32_t out_sat, hipStream_t stream)
+                              uint32_t in_sat, uint32_t out_sat, uint32_t *full,
+                              hipStream_t stream)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_hull_counts, dim3((unsigned)((n + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, stream, g, h, n, wepl_in, wepl_out, in_cnt, out_cnt,
-                       in_sat, out_sat);
+    const int64_t nvox = (int64_t)g.nx * g.ny * g.nz, nw = (nvox + 31) / 32;
+    // The first lines fill most voxels; every later stage reads which are
+    // full from bits that do not change while it runs (256 KB at 256x256x32:
+    // they stay in the caches, where the counters themselves are read past
+    // them).  8M lines of 256x256x32: 5.7 ms, bound by instruction issue (two
+    // thirds of the lanes idle in the average piece); 16.6 ms without stages and
+    // with a midpoint per piece.
+    const int64_t stage[3] = {std::min<int64_t>(n, std::max<int64_t>(n / 64, 65536)),
+                              std::min<int64_t>(n, std::max<int64_t>(n / 8, 262144)), n};
+    int64_t first = 0;
+    for (int q = 0; q < 3; q++) {
+        const int64_t end = stage[q];
+        if (end <= first) continue;
+        HullCounts c{in_cnt, out_cnt, nullptr, nullptr, in_sat, out_sat};
+        if (first > 0) {
+            hipLaunchKernelGGL(k_hull_full, dim3((unsigned)((nvox + kThreads - 1) / kThreads)),
+                               dim3(kThreads), 0, stream, in_cnt, out_cnt, nvox, in_sat, out_sat,
+                               full, nw);
+            c.in_full = full;
+            c.out_full = full + nw;
+        }
+        hipLaunchKernelGGL(k_hull_counts, dim3((unsigned)((end - first + kThreads - 1) / kThreads)),
+                           dim3(kThreads), 0, stream, g, h, first, end, wepl_in, wepl_out, c);
+        first = end;
+    }
     return hipGetLastError();
 }
 

@@ -1668,21 +1668,23 @@ int tvs_hull_detect(tvs_ctx *ctx, const tvs_hull_params *p, uint8_t *hull, int o
     hipStream_t st = pick(ctx, stream);
     uint32_t *cnt = nullptr;
     uint8_t *hd = nullptr;
-    int rc = dalloc(ctx, &cnt, (size_t)(2 * ctx->nvox));
-    if (!rc) rc = dalloc(ctx, &hd, (size_t)ctx->nimg);
+    // the mask's buffer holds the full-voxel bits until the mask is written
+    const size_t nhd = std::max((size_t)ctx->nimg, (size_t)(4 * tvs::hull_full_words(ctx->gd)));
+    int rc = dalloc(ctx, &cnt, (size_t)(2 * ctx->nimg));
+    if (!rc) rc = dalloc(ctx, &hd, nhd);
     if (rc) {
-        dfree(ctx, &cnt, (size_t)(2 * ctx->nvox));
+        dfree(ctx, &cnt, (size_t)(2 * ctx->nimg));
         return rc;
     }
     // the counting threshold -inf when space modelling is off makes every
     // line count; min_in = 0 then accepts every voxel on that side
-    hipError_t e = hipMemsetAsync(cnt, 0, sizeof(uint32_t) * 2 * ctx->nvox, st);
+    hipError_t e = hipMemsetAsync(cnt, 0, sizeof(uint32_t) * 2 * ctx->nimg, st);
     if (e == hipSuccess)
         e = tvs::launch_hull_counts(ctx->gd, hist_dev(ctx), ctx->nh, p->wepl_in_mm, p->wepl_out_mm,
-                                    cnt, cnt + ctx->nvox, (uint32_t)p->min_in,
-                                    (uint32_t)p->max_out + 1u, st);
+                                    cnt, cnt + ctx->nimg, (uint32_t)p->min_in,
+                                    (uint32_t)p->max_out + 1u, reinterpret_cast<uint32_t *>(hd), st);
     if (e == hipSuccess)
-        e = tvs::launch_hull_decide(ctx->gd, cnt, cnt + ctx->nvox, (uint32_t)p->min_in,
+        e = tvs::launch_hull_decide(ctx->gd, cnt, cnt + ctx->nimg, (uint32_t)p->min_in,
                                     (uint32_t)p->max_out, hd, p->mask_image ? ctx->x : nullptr, st);
     if (e == hipSuccess && p->mask_image)
         e = hipMemcpyAsync(ctx->x0, ctx->x, sizeof(double) * ctx->nvox, hipMemcpyDeviceToDevice, st);
@@ -1690,8 +1692,8 @@ int tvs_hull_detect(tvs_ctx *ctx, const tvs_hull_params *p, uint8_t *hull, int o
         e = hipMemcpyAsync(hull, hd, (size_t)ctx->nimg,
                            on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    dfree(ctx, &cnt, (size_t)(2 * ctx->nvox));
-    dfree(ctx, &hd, (size_t)ctx->nimg);
+    dfree(ctx, &cnt, (size_t)(2 * ctx->nimg));
+    dfree(ctx, &hd, nhd);
     if (e != hipSuccess) return fail(ctx, TVS_EDEVICE, std::string("hull: ") + hipGetErrorString(e));
     if (p->mask_image) {
         reset_state(ctx);

@@ -81,3 +81,23 @@ def test_rows_of_curved_paths(n):
         h[k] = rng.uniform(-1.0, 1.0, n).astype(np.float32)
     for step in (0.3, 1.0):
         check(grid, h, step, "otf")
+
+
+@pytest.mark.parametrize("dims,vox,n", [((17, 16, 3), (1.0, 1.0, 2.5), 70_000),
+                                        ((1, 1, 1), (2.0, 2.0, 2.0), 500),
+                                        ((33, 5, 1), (1.3, 0.7, 2.0), 300_000),
+                                        ((64, 64, 2), (1.0, 1.0, 1.0), 300_000)])
+def test_hull_of_lines_on_planes(dims, vox, n):
+    """Hull counts of the same kind of lines, through one, two and three stages
+    (65,536 and 262,144 lines), with counts low enough to fill and too high."""
+    grid = synth.centered_grid(*dims, *vox)
+    h = lines(grid, n, n + dims[0])
+    with tvs.Context(grid, block_size=3200) as ctx:
+        ctx.load_histories(h)
+        for min_in, max_out in ((1, 0), (0, 3), (n // 40, n // 300), (n // 10, n)):
+            got = ctx.hull_detect(wepl_in_mm=10.0, wepl_out_mm=12.0, min_in=min_in,
+                                  max_out=max_out)
+            want = oracle.hull(grid, h, wepl_in=10.0, wepl_out=12.0, min_in=min_in,
+                               max_out=max_out)
+            print(f"hull {dims} {min_in} {max_out}: inside {int(want.sum())}", flush=True)
+            np.testing.assert_array_equal(got, want)
