@@ -47,10 +47,13 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "device_common.hpp"
 #include "tvs_internal.hpp"
 
 namespace tvs {
 namespace {
+
+using dev::round_scaled;
 
 constexpr int kShards = kChainShards;
 constexpr uint32_t kNone = 0xffffffffu;   // no entry; an empty table slot
@@ -63,13 +66,6 @@ constexpr int kRing = 8;                  // blocks whose list starts are held
 constexpr double kDotUnit = 1.0 / kDotScale;
 constexpr double kCorrUnit = 1.0 / kCorrScale;
 constexpr uint64_t kWaitTicks = 3000000000ull;   // 30 s of the 100 MHz clock
-
-// v rounded to nearest (ties to even) as an integer, for |v| < 2^51: adding
-// 1.5 2^52 leaves the integer in the low mantissa bits.
-__device__ inline long long round_small(double v)
-{
-    return __double_as_longlong(v + 6755399441055744.0) - 0x4338000000000000ll;
-}
 
 template <typename T>
 __device__ inline T load_agent(const T *p)
@@ -409,7 +405,7 @@ struct Chain {
         for (int i = 0; i < E; i++) p[i] = (double)en.a[i] * L.x[word(en.pk[i])];
 #pragma unroll
         for (int i = 0; i < E; i++) {
-            f[i] = round_small(p[i] * kDotScale);
+            f[i] = round_scaled(p[i], kDotScale);
             rare |= !(fabs(p[i]) <= A.dot_small);
         }
         if (rare) {
@@ -457,7 +453,7 @@ struct Chain {
         if (!(rare || (loose & kLoose))) {
 #pragma unroll
             for (int i = 0; i < E; i++)
-                if (FULL || i < en.n) lds_add(L.cf + word(en.pk[i]), round_small(v[i] * kCorrScale));
+                if (FULL || i < en.n) lds_add(L.cf + word(en.pk[i]), round_scaled(v[i], kCorrScale));
             return;
         }
 #pragma unroll 1

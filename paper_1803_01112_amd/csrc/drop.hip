@@ -42,6 +42,8 @@ using dev::row_of;
 
 constexpr double kDotUnit = 1.0 / kDotScale;
 constexpr double kCorrUnit = 1.0 / kCorrScale;
+// magnitudes up to which the scaled values stay below 2^51
+constexpr double kSmallDot = 16384.0, kSmallCorr = 1024.0;
 
 // LDS of one tile workgroup.
 struct TileLds {
@@ -105,7 +107,8 @@ __device__ inline void finish_one(const TileBlock &P, const Ent &en, const RowDa
     atomicAdd(&L.hits[w], 1u);
     if (fabs(v) <= big)
         atomicAdd(reinterpret_cast<unsigned long long *>(&L.cf[w]),
-                  (unsigned long long)__double2ll_rn(v * kCorrScale));
+                  (unsigned long long)(fabs(v) <= kSmallCorr ? dev::round_scaled(v, kCorrScale)
+                                                             : __double2ll_rn(v * kCorrScale)));
     else
         atomicAdd(&L.cb[w], v);
 }
@@ -164,7 +167,8 @@ __device__ void tile_dots(const TileBlock &C, int64_t c0, int64_t c1, const Ent 
                 atomicOr(err, 2u);
                 q = kNoRow;
             } else if (fabs(p) <= dot_max) {
-                f = __double2ll_rn(p * kDotScale);
+                f = fabs(p) <= kSmallDot ? dev::round_scaled(p, kDotScale)
+                                         : __double2ll_rn(p * kDotScale);
             } else {
                 atomicOr(err, 1u);
             }
