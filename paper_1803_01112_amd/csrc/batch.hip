@@ -43,10 +43,9 @@ __host__ __device__ inline Place place(int64_t nvox, int S, int s)
 // Thread t of a workgroup handles setting s = t % S of voxel w*V + t / S.
 __global__ void __launch_bounds__(kThreads)
 k_tvb_grad(GridDev G, const double *x, int S, int V, uint32_t active, const double *eps,
-           double *g, double *part, uint32_t *ticket, double *norm2)
+           double *g, double *part)
 {
     __shared__ double red[kThreads];
-    __shared__ uint32_t last;
     const int t = threadIdx.x;
     const int v = t / S, s = t - v * S;
     const int64_t nx = G.nx, ny = G.ny;
@@ -94,29 +93,28 @@ k_tvb_grad(GridDev G, const double *x, int S, int V, uint32_t active, const doub
         for (int vv = 0; vv < V; vv++) a += red[vv * S + t];
         part[(int64_t)blockIdx.x * S + t] = a;
     }
-    __syncthreads();
-    if (t == 0) {
-        __threadfence();
-        uint32_t old = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        last = (old == gridDim.x - 1u);
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
+}
+
+// Squared norms from the partials, one workgroup per setting: thread v adds
+// those of every V-th workgroup of the gradient, then the V sums in order.  A
+// launch of its own: handing the partials over inside the gradient's launch
+// made its workgroups write back the L2's dirty lines (300 us a gradient of 24
+// settings of 200x200x16 against 248 and 3 for this launch).
+__global__ void __launch_bounds__(kThreads)
+k_tvb_norm(const double *part, uint32_t n, int S, int V, double *norm2)
+{
+    __shared__ double red[kThreads];
+    const int v = threadIdx.x, s = blockIdx.x;
     double a = 0.0;
     if (v < V)
-        for (uint32_t w = v; w < gridDim.x; w += V)
-            a += __hip_atomic_load(part + (int64_t)w * S + s, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+        for (uint32_t w = v; w < n; w += V) a += part[(int64_t)w * S + s];
+    red[v] = a;
     __syncthreads();
-    red[t] = a;
-    __syncthreads();
-    if (t < S) {
+    if (v == 0) {
         double b = 0.0;
-        for (int vv = 0; vv < V; vv++) b += red[vv * S + t];
-        norm2[t] = b;
+        for (int vv = 0; vv < V; vv++) b += red[vv];
+        norm2[s] = b;
     }
-    if (t == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Setting and word of element q of an S-image buffer.
@@ -411,7 +409,9 @@ hipError_t launch_tvb_grad(const GridDev &g, const BatchBuffers &b, uint32_t act
 {
     const int V = batch_vox_per_wg(b.S);
     hipLaunchKernelGGL(k_tvb_grad, dim3((unsigned)batch_num_parts(g, b.S)), dim3(V * b.S), 0,
-                       stream, g, b.x, b.S, V, active, b.eps, b.g, b.part, b.ticket, b.norm2);
+                       stream, g, b.x, b.S, V, active, b.eps, b.g, b.part);
+    hipLaunchKernelGGL(k_tvb_norm, dim3((unsigned)b.S), dim3(kThreads), 0, stream,
+                       (const double *)b.part, (uint32_t)batch_num_parts(g, b.S), b.S, V, b.norm2);
     return hipGetLastError();
 }
 

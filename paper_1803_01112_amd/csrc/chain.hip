@@ -53,6 +53,7 @@
 namespace tvs {
 namespace {
 
+using dev::drain_memory;
 using dev::round_scaled;
 
 constexpr int kShards = kChainShards;
@@ -99,8 +100,6 @@ __device__ inline uint32_t lds_add(uint32_t *p, uint32_t v)
 {
     return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-// This wave's memory operations are complete at the point of coherence.
-__device__ inline void drain_memory() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 
 struct Lds {
     double *x;

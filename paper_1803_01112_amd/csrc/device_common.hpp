@@ -100,5 +100,9 @@ __device__ inline long long round_scaled(double v, double scale)
     return __double_as_longlong(fma(v, scale, 6755399441055744.0)) - 0x4338000000000000ll;
 }
 
+// This wave's memory operations are complete; its agent-scope stores and atomics
+// are then visible to the whole device.
+__device__ inline void drain_memory() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
+
 }  // namespace dev
 }  // namespace tvs

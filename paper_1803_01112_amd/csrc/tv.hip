@@ -13,9 +13,13 @@
 // turn its rounding into order-one changes of v.  A workgroup stages 64x4
 // tiles of one slice plus a one-voxel halo in LDS (a grid of at most 1024
 // workgroups strides over the tiles), evaluates the stencil, and writes a
-// float64 partial sum.  The last workgroup to finish (ticket counter) adds
-// the partials in a fixed order, so every reduction is deterministic and no
-// host round trip is needed between the gradient and the update.
+// float64 partial sum.  Every workgroup of the kernels that need the norm adds
+// the partials itself, in a fixed order, so the reduction is deterministic,
+// needs no host round trip, and the gradient's workgroups need not publish
+// what they wrote within their launch.
+#include <algorithm>
+
+#include "device_common.hpp"
 #include "tvs_internal.hpp"
 
 namespace tvs {
@@ -38,9 +42,8 @@ __device__ inline void load_tile(double (*t)[HX], const double *x, const GridDev
     __syncthreads();
 }
 
-__device__ inline double step_scale(double beta, const double *n2)
+__device__ inline double step_scale(double beta, double nn)
 {
-    double nn = *n2;
     return (nn > 0.0) ? -beta / sqrt(nn) : 0.0;
 }
 
@@ -72,34 +75,21 @@ __device__ inline double block_sum(double v)
     return tot;   // valid in thread 0
 }
 
-// Writes this workgroup's partial; the last workgroup reduces all partials
-// in a fixed order into *out and re-arms the ticket.  The partials are read
-// with plain loads after the acquire that observed the last ticket (every
-// writer released its partial before taking a ticket), four in flight per
-// lane.
-__device__ inline void finish_reduction(double partial, double *part, uint32_t *ticket,
-                                        double *out)
+// Sum of the gradient's partials in a fixed order, in every thread (at most
+// kMaxWgs of them, 8 KB from the L2: some 2 us).  Handing it over inside the
+// gradient's launch, by a last workgroup and a ticket, made each workgroup
+// write back the L2's dirty lines, the subgradient's among them: 28 to 133 us
+// a gradient at 200x200x16 against 12.8.
+__device__ inline double sum_parts(const double *part, uint32_t n)
 {
-    __shared__ uint32_t last;
-    const uint32_t nwg = gridDim.x;
-    if (threadIdx.x == 0) {
-        part[blockIdx.x] = partial;
-        __threadfence();
-        uint32_t old = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL,
-                                              __HIP_MEMORY_SCOPE_AGENT);
-        last = (old == nwg - 1u);
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
+    __shared__ double all;
     double v = 0.0;
 #pragma unroll 4
-    for (uint32_t q = threadIdx.x; q < nwg; q += kThreads) v += part[q];
-    double tot = block_sum(v);
-    if (threadIdx.x == 0) {
-        *out = tot;
-        __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    for (uint32_t q = threadIdx.x; q < n; q += kThreads) v += part[q];
+    const double tot = block_sum(v);
+    if (threadIdx.x == 0) all = tot;
+    __syncthreads();
+    return all;
 }
 
 // Tiles of TX x TY voxels of one slice; a capped grid of workgroups strides
@@ -124,8 +114,7 @@ __device__ inline TileGrid tile_grid(const GridDev &G)
 }
 
 __global__ void __launch_bounds__(kThreads)
-k_tv_grad(GridDev G, const double *x, double eps, double *gout, double *part, uint32_t *ticket,
-          double *out)
+k_tv_grad(GridDev G, const double *x, double eps, double *gout, double *part)
 {
     __shared__ double tile[HY][HX];
     const TileGrid TG = tile_grid(G);
@@ -153,7 +142,8 @@ k_tv_grad(GridDev G, const double *x, double eps, double *gout, double *part, ui
             sq += gv * gv;
         }
     }
-    finish_reduction(block_sum(sq), part, ticket, out);
+    const double tot = block_sum(sq);
+    if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
 // ---------------------------------------------------------------- checked step
@@ -249,7 +239,7 @@ __device__ inline void block_sums(const double *v, double *out)
 }
 
 __global__ void __launch_bounds__(kThreads)
-k_tv_check(GridDev G, const double *x, const double *g, const double *n2, double eps,
+k_tv_check(GridDev G, const double *x, const double *g, const double *gpart, double eps,
            double alpha, int32_t max_tries, int32_t k, int32_t n, SchedDev *sd, tvs_step_log *rec,
            double *part, uint32_t *ticket, double *dec)
 {
@@ -259,7 +249,7 @@ k_tv_check(GridDev G, const double *x, const double *g, const double *n2, double
     __shared__ uint32_t last;
     const TileGrid TG = tile_grid(G);
     const int64_t ell0 = sd->ell;
-    const double gn2 = *n2;
+    const double gn2 = sum_parts(gpart, gridDim.x);   // the gradient's grid
     const int cnt0 = max_tries < kTries ? max_tries : kTries;
     if (threadIdx.x < kTries) sc[threadIdx.x] = trial_scale(alpha, ell0 + threadIdx.x, gn2);
     double acc[kTries + 1];
@@ -277,23 +267,26 @@ k_tv_check(GridDev G, const double *x, const double *g, const double *n2, double
     const uint32_t nwg = gridDim.x;
     const uint32_t wg = blockIdx.x;
     if (threadIdx.x == 0) {
-        for (int t = 0; t <= kTries; t++) part[(int64_t)t * nwg + wg] = tot[t];
-        __threadfence();
-        const uint32_t old = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL,
+        for (int t = 0; t <= kTries; t++)
+            __hip_atomic_store(part + (int64_t)t * nwg + wg, tot[t], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        dev::drain_memory();
+        const uint32_t old = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_AGENT);
         last = (old == nwg - 1u);
     }
     __syncthreads();
     if (!last) return;
-    __threadfence();
-    // plain loads after the acquire above (every writer released its
-    // partials before taking a ticket), kTries + 1 in flight per lane
+    // read past the caches, kTries + 1 in flight per lane: every writer's
+    // partials had left its caches before it took a ticket
     double v[kTries + 1];
 #pragma unroll
     for (int t = 0; t <= kTries; t++) v[t] = 0.0;
     for (uint32_t q = threadIdx.x; q < nwg; q += kThreads) {
 #pragma unroll
-        for (int t = 0; t <= kTries; t++) v[t] += part[(int64_t)t * nwg + q];
+        for (int t = 0; t <= kTries; t++)
+            v[t] += __hip_atomic_load(part + (int64_t)t * nwg + q, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
     }
     block_sums(v, tot);
     const double phx = tot[kTries];
@@ -381,9 +374,9 @@ __global__ void k_sched_set(SchedDev *sd, int64_t ell, uint64_t rng)
 }
 
 __global__ void __launch_bounds__(kThreads)
-k_tv_step(double *x, const double *g, int64_t n, double beta, const double *n2)
+k_tv_step(double *x, const double *g, int64_t n, double beta, const double *part, uint32_t nparts)
 {
-    const double s = step_scale(beta, n2);
+    const double s = step_scale(beta, sum_parts(part, nparts));
     if (s == 0.0) return;
     for (int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x; p < n;
          p += (int64_t)gridDim.x * kThreads)
@@ -438,8 +431,7 @@ int64_t tv_num_parts(const GridDev &g)
 hipError_t launch_tv_grad(const GridDev &g, const double *x, double eps, const TvBuffers &t,
                           hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_tv_grad, tv_grid(g), dim3(kThreads), 0, stream, g, x, eps, t.g, t.part,
-                       t.ticket, t.scal);
+    hipLaunchKernelGGL(k_tv_grad, tv_grid(g), dim3(kThreads), 0, stream, g, x, eps, t.g, t.part);
     return hipGetLastError();
 }
 
@@ -447,8 +439,9 @@ hipError_t launch_tv_step(const GridDev &g, double *x, double beta, const TvBuff
                           hipStream_t stream)
 {
     const int64_t n = padded_voxels(g);   // the padding's subgradient is zero
-    hipLaunchKernelGGL(k_tv_step, dim3(elem_grid(n)), dim3(kThreads), 0, stream, x, t.g, n, beta,
-                       t.scal);
+    const unsigned wgs = std::min(elem_grid(n), (unsigned)kMaxWgs);   // each adds the partials
+    hipLaunchKernelGGL(k_tv_step, dim3(wgs), dim3(kThreads), 0, stream, x, (const double *)t.g, n,
+                       beta, (const double *)t.part, (uint32_t)t.nparts);
     return hipGetLastError();
 }
 
@@ -474,7 +467,7 @@ hipError_t launch_tv_check(const GridDev &g, const double *x, double eps, double
                            hipStream_t stream)
 {
     hipLaunchKernelGGL(k_tv_check, tv_grid(g), dim3(kThreads), 0, stream, g, x,
-                       (const double *)t.g, (const double *)t.scal, eps, alpha, max_tries, k, n,
+                       (const double *)t.g, (const double *)t.part, eps, alpha, max_tries, k, n,
                        sd, rec, c.part, c.ticket, c.dec);
     return hipGetLastError();
 }

@@ -358,7 +358,6 @@ void free_batch(tvs_ctx *ctx)
     dfree(ctx, &B.b.x, n);
     dfree(ctx, &B.b.g, n);
     dfree(ctx, &B.b.part, (size_t)(tvs::batch_num_parts(ctx->gd, std::max(B.S, 1)) * B.S));
-    dfree(ctx, &B.b.ticket, (size_t)4);
     dfree(ctx, &B.b.norm2, (size_t)B.S);
     dfree(ctx, &B.b.lambda, (size_t)B.S);
     dfree(ctx, &B.b.eps, (size_t)B.S);
@@ -375,7 +374,7 @@ HistDev hist_dev(const tvs_ctx *ctx)
 
 tvs::TvBuffers tv_bufs(tvs_ctx *ctx)
 {
-    return tvs::TvBuffers{ctx->g, ctx->part, ctx->ticket, ctx->scal, ctx->nparts};
+    return tvs::TvBuffers{ctx->g, ctx->part, ctx->nparts};
 }
 
 hipStream_t pick(tvs_ctx *ctx, void *stream)
@@ -1976,7 +1975,6 @@ int batch_init(tvs_ctx *ctx, const tvs_params *p, int S, hipStream_t st)
         int rc = dalloc(ctx, &B.b.x, n);
         if (!rc) rc = dalloc(ctx, &B.b.g, n);
         if (!rc) rc = dalloc(ctx, &B.b.part, (size_t)(tvs::batch_num_parts(ctx->gd, S) * S));
-        if (!rc) rc = dalloc(ctx, &B.b.ticket, (size_t)4);
         if (!rc) rc = dalloc(ctx, &B.b.norm2, (size_t)S);
         if (!rc) rc = dalloc(ctx, &B.b.lambda, (size_t)S);
         if (!rc) rc = dalloc(ctx, &B.b.eps, (size_t)S);
@@ -1988,7 +1986,6 @@ int batch_init(tvs_ctx *ctx, const tvs_params *p, int S, hipStream_t st)
         }
         B.b.S = S;
         B.b.nvox = ctx->nvox;
-        HIPCHK(hipMemsetAsync(B.b.ticket, 0, sizeof(uint32_t) * 4, st));
         HIPCHK(hipMemsetAsync(B.b.g, 0, sizeof(double) * n, st));
     }
     B.p.assign(p, p + S);

@@ -332,9 +332,7 @@ hipError_t launch_chain(const ChainArgs &a, hipStream_t stream);
 // ----------------------------------------------------------------- tv.hip
 struct TvBuffers {
     double *g;           // subgradient
-    double *part;        // per-workgroup partial sums
-    uint32_t *ticket;    // last-workgroup counter
-    double *scal;        // [0] = ||g||^2, [1] = phi value
+    double *part;        // per-workgroup partial sums of ||g||^2
     int64_t nparts;
 };
 int64_t tv_num_parts(const GridDev &g);
@@ -354,7 +352,7 @@ struct CheckBuffers {
 };
 int64_t tv_check_parts(const GridDev &g);
 // One checked step: decides on the device (first try t with
-// TV(x + s_t g) <= TV(x), s_t = -alpha^(ell + t) / sqrt(scal[0]), at most
+// TV(x + s_t g) <= TV(x), s_t = -alpha^(ell + t) / ||g||, at most
 // max_tries tries), advances sd->ell by the tries and writes *rec.
 hipError_t launch_tv_check(const GridDev &g, const double *x, double eps, double alpha,
                            int32_t max_tries, int32_t k, int32_t n, SchedDev *sd,
@@ -366,10 +364,11 @@ hipError_t launch_tv_apply(const GridDev &g, double *x, const TvBuffers &t, cons
 // ell = rand(k, ell) with the device SplitMix64 state; sets the state.
 hipError_t launch_sched_draw(SchedDev *sd, int64_t k, hipStream_t stream);
 hipError_t launch_sched_set(SchedDev *sd, int64_t ell, uint64_t rng, hipStream_t stream);
-// g = grad TV(x); scal[0] = ||g||^2 (fixed-order reduction).
+// g = grad TV(x), and the partial sums of ||g||^2.
 hipError_t launch_tv_grad(const GridDev &g, const double *x, double eps, const TvBuffers &t,
                           hipStream_t stream);
-// x = x + s * g with s = -beta / sqrt(scal[0]) (0 when the norm is 0).
+// x = x + s * g with s = -beta / ||g|| (0 when the norm is 0; the partials are
+// added in a fixed order).
 hipError_t launch_tv_step(const GridDev &g, double *x, double beta, const TvBuffers &t,
                           hipStream_t stream);
 // Image conversion between the ABI's x-fastest float32 and the device's
@@ -385,7 +384,6 @@ struct BatchBuffers {
     double *x = nullptr;        // nvox * S
     double *g = nullptr;        // nvox * S
     double *part = nullptr;     // batch_num_parts * S
-    uint32_t *ticket = nullptr;
     double *norm2 = nullptr;    // S
     double *lambda = nullptr;   // S
     double *eps = nullptr;      // S
@@ -394,6 +392,7 @@ struct BatchBuffers {
 };
 int batch_vox_per_wg(int S);
 int64_t batch_num_parts(const GridDev &g, int S);
+// the subgradients of the active settings and their squared norms (two launches)
 hipError_t launch_tvb_grad(const GridDev &g, const BatchBuffers &b, uint32_t active,
                            hipStream_t stream);
 hipError_t launch_tvb_step(const BatchBuffers &b, uint32_t active, int n, int nmax,
