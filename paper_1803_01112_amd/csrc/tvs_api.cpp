@@ -127,6 +127,7 @@ struct tvs_ctx {
     int64_t nvox = 0;               // words of a device image (tiled layout, padding included)
     int64_t nimg = 0;               // voxels of an image at the ABI (nx * ny * nz)
     int64_t ntiles = 0;
+    int cus = 256;
     uint64_t budget = 0;
     uint64_t bytes = 0;
     std::string err;
@@ -1271,6 +1272,7 @@ int tvs_create(const tvs_grid *grid, const tvs_config *cfg_in, tvs_ctx **out)
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg.device) !=
             hipSuccess)
             cus = 0;
+        if (cus > 0) ctx->cus = cus;
         const int per_cu = cfg.fill_wgs_per_cu;
         ctx->fill_wgs = (per_cu > 0 && cus > 0) ? (int64_t)per_cu * cus : 0;
         // the library's choice: about 40 % of the chunks at full occupancy
@@ -1524,27 +1526,16 @@ int tvs_initial_fbp(tvs_ctx *ctx, const tvs_fbp_params *p, float *out, int on_de
     const tvs_grid &g = ctx->grid;
     const int32_t A = p->n_angles;
 
-    unsigned long long *sum = nullptr;
-    uint32_t *cnt = nullptr;
-    double *pb = nullptr, *qb = nullptr, *cs = nullptr, *img = nullptr;
-    auto release = [&]() {
-        dfree(ctx, &sum, (size_t)nb);
-        dfree(ctx, &cnt, (size_t)nb);
-        dfree(ctx, &pb, (size_t)nb);
-        dfree(ctx, &qb, (size_t)nb);
-        dfree(ctx, &cs, (size_t)(2 * A));
-        dfree(ctx, &img, (size_t)ctx->nimg);
-    };
-    rc = dalloc(ctx, &sum, (size_t)nb);
-    if (!rc) rc = dalloc(ctx, &cnt, (size_t)nb);
-    if (!rc) rc = dalloc(ctx, &pb, (size_t)nb);
-    if (!rc) rc = dalloc(ctx, &qb, (size_t)nb);
-    if (!rc) rc = dalloc(ctx, &cs, (size_t)(2 * A));
-    if (!rc) rc = dalloc(ctx, &img, (size_t)ctx->nimg);
-    if (rc) {
-        release();
-        return rc;
-    }
+    // one allocation: 20 B per bin (a sum and a count each, then the filter's
+    // taps; the filtered projections over the former), the means, the angle
+    // table, the image.  nt is even.
+    const size_t words = (size_t)nb / 2 * 5 + (size_t)nb + (size_t)(2 * A) + (size_t)ctx->nimg;
+    double *work = nullptr;
+    rc = dalloc(ctx, &work, words);
+    if (rc) return rc;
+    auto *slots = reinterpret_cast<unsigned long long *>(work);
+    double *qb = work, *taps = work + 2 * nb, *pb = work + nb / 2 * 5, *cs = pb + nb;
+    double *img = cs + 2 * A;
     // cos, sin of every beam angle a * 2 pi / A
     std::vector<double> tab((size_t)(2 * A));
     const double da = 2.0 * 3.14159265358979323846 / (double)A;
@@ -1553,12 +1544,10 @@ int tvs_initial_fbp(tvs_ctx *ctx, const tvs_fbp_params *p, float *out, int on_de
         tab[(size_t)(2 * a)] = std::cos(phi);
         tab[(size_t)(2 * a + 1)] = std::sin(phi);
     }
-    hipError_t e = hipMemsetAsync(sum, 0, sizeof(unsigned long long) * nb, st);
-    if (e == hipSuccess) e = hipMemsetAsync(cnt, 0, sizeof(uint32_t) * nb, st);
+    hipError_t e = hipMemsetAsync(slots, 0, sizeof(unsigned long long) * 2 * nb, st);
     if (e == hipSuccess) e = hipMemcpyAsync(cs, tab.data(), sizeof(double) * 2 * A, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = tvs::launch_fbp_bin(ctx->gd, hist_dev(ctx), ctx->nh, A, tau, nt, sum, cnt, st);
-    if (e == hipSuccess) e = tvs::launch_fbp_mean(sum, cnt, nb, pb, st);
-    if (e == hipSuccess) e = tvs::launch_fbp_filter(pb, (int64_t)A * g.nz, nt, tau, qb, st);
+    if (e == hipSuccess) e = tvs::launch_fbp_bin(ctx->gd, hist_dev(ctx), ctx->nh, A, tau, nt, ctx->cus, slots, st);
+    if (e == hipSuccess) e = tvs::launch_fbp_filter(slots, (int64_t)A * g.nz, nt, tau, taps, pb, st);
     if (e == hipSuccess)
         e = tvs::launch_fbp_backproject(ctx->gd, qb, cs, A, tau, nt, p->clip_negative ? 1 : 0, img, st);
     if (e == hipSuccess) e = tvs::launch_median(ctx->gd, img, p->median_radius, ctx->xio, st);
@@ -1571,7 +1560,7 @@ int tvs_initial_fbp(tvs_ctx *ctx, const tvs_fbp_params *p, float *out, int on_de
         e = hipMemcpyAsync(out, ctx->xio, sizeof(float) * ctx->nimg,
                            on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    release();
+    dfree(ctx, &work, words);
     if (e != hipSuccess) return fail(ctx, TVS_EDEVICE, std::string("initial fbp: ") + hipGetErrorString(e));
     reset_state(ctx);
     ctx->batch.valid = false;
@@ -1589,13 +1578,12 @@ int tvs_initial_fbp_noalloc(tvs_ctx *ctx, const tvs_fbp_params *p, float *out, i
     int rc = fbp_geometry(ctx, p, "tvs_initial_fbp_noalloc", tau, nt, nb);
     if (rc) return rc;
     const int32_t A = p->n_angles;
-    // workspace layout: bin sums and counts (cleared), mean and filtered
-    // projections, angle table, backprojected image; each part 256-aligned
-    const size_t o_sum = 0;
-    const size_t o_cnt = o_sum + align256(sizeof(unsigned long long) * (size_t)nb);
-    const size_t o_pb = o_cnt + align256(sizeof(uint32_t) * (size_t)nb);
-    const size_t o_qb = o_pb + align256(sizeof(double) * (size_t)nb);
-    const size_t o_cs = o_qb + align256(sizeof(double) * (size_t)nb);
+    // workspace layout: bin sums and counts (cleared) in 16 of the 20 B per bin
+    // up to o_pb, the filter's taps behind them, the filtered projections over
+    // the former, means, angle table, backprojected image; each part 256-aligned
+    const size_t nbw = align256(sizeof(double) * (size_t)nb);
+    const size_t o_pb = 2 * nbw + align256(sizeof(uint32_t) * (size_t)nb);
+    const size_t o_cs = o_pb + nbw;
     const size_t o_img = o_cs + align256(sizeof(double) * 2 * (size_t)A);
     const size_t need = o_img + align256(sizeof(double) * (size_t)ctx->nimg);
     if (need > kFbpScratchBytes)
@@ -1619,21 +1607,18 @@ int tvs_initial_fbp_noalloc(tvs_ctx *ctx, const tvs_fbp_params *p, float *out, i
         base = static_cast<unsigned char *>(g_scratch_ptr[dev]);
     }
     hipStream_t st = pick(ctx, stream);
-    auto *sum = reinterpret_cast<unsigned long long *>(base + o_sum);
-    auto *cnt = reinterpret_cast<uint32_t *>(base + o_cnt);
-    auto *pb = reinterpret_cast<double *>(base + o_pb);
-    auto *qb = reinterpret_cast<double *>(base + o_qb);
+    auto *slots = reinterpret_cast<unsigned long long *>(base);
+    auto *taps = reinterpret_cast<double *>(slots + 2 * nb);
+    auto *qb = reinterpret_cast<double *>(base), *pb = reinterpret_cast<double *>(base + o_pb);
     auto *cs = reinterpret_cast<double *>(base + o_cs);
     auto *img = reinterpret_cast<double *>(base + o_img);
     const tvs_grid &g = ctx->grid;
     // sums and counts start at zero (a fill kernel: the workspace keeps the
     // previous call's contents)
-    hipError_t e = tvs::launch_zero_i64(reinterpret_cast<long long *>(base + o_sum),
-                                        (int64_t)(o_pb / sizeof(long long)), st);
+    hipError_t e = tvs::launch_zero_i64(reinterpret_cast<long long *>(slots), 2 * nb, st);
     if (e == hipSuccess) e = tvs::launch_fbp_angles(A, cs, st);
-    if (e == hipSuccess) e = tvs::launch_fbp_bin(ctx->gd, hist_dev(ctx), ctx->nh, A, tau, nt, sum, cnt, st);
-    if (e == hipSuccess) e = tvs::launch_fbp_mean(sum, cnt, nb, pb, st);
-    if (e == hipSuccess) e = tvs::launch_fbp_filter(pb, (int64_t)A * g.nz, nt, tau, qb, st);
+    if (e == hipSuccess) e = tvs::launch_fbp_bin(ctx->gd, hist_dev(ctx), ctx->nh, A, tau, nt, ctx->cus, slots, st);
+    if (e == hipSuccess) e = tvs::launch_fbp_filter(slots, (int64_t)A * g.nz, nt, tau, taps, pb, st);
     if (e == hipSuccess)
         e = tvs::launch_fbp_backproject(ctx->gd, qb, cs, A, tau, nt, p->clip_negative ? 1 : 0, img, st);
     if (e == hipSuccess) e = tvs::launch_median(ctx->gd, img, p->median_radius, ctx->xio, st);

@@ -206,12 +206,13 @@ hipError_t launch_hull_decide(const GridDev &g, const uint32_t *in_cnt, const ui
 // dst[b] = src[b * stride] for b < n.
 // Initial iterate (fbp.hip): binning, Ram-Lak filter, backprojection,
 // in-slice median (radius 0..2; 0 only narrows the image to float32).
+// slots: a sum and a count per bin (16 B); the filter writes the means to p and
+// its taps to `taps` (nt / 2 doubles), then the filtered projections over the
+// slots (8 B per bin).
 hipError_t launch_fbp_bin(const GridDev &g, const HistDev &h, int64_t n, int32_t A, double tau,
-                          int32_t nt, unsigned long long *sum, uint32_t *cnt, hipStream_t stream);
-hipError_t launch_fbp_mean(const unsigned long long *sum, const uint32_t *cnt, int64_t nb, double *p,
-                           hipStream_t stream);
-hipError_t launch_fbp_filter(const double *p, int64_t rows, int32_t nt, double tau, double *q,
-                             hipStream_t stream);
+                          int32_t nt, int32_t cus, unsigned long long *slots, hipStream_t stream);
+hipError_t launch_fbp_filter(unsigned long long *slots, int64_t rows, int32_t nt, double tau,
+                             double *taps, double *p, hipStream_t stream);
 hipError_t launch_fbp_backproject(const GridDev &g, const double *q, const double *cs, int32_t A,
                                   double tau, int32_t nt, int clip, double *x, hipStream_t stream);
 hipError_t launch_median(const GridDev &g, const double *x, int radius, float *out,

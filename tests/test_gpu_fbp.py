@@ -71,3 +71,26 @@ def test_rejects_bad_parameters():
                    dict(n_angles=90, t_bin_mm=-1.0)):
             with pytest.raises(tvs.TvsError):
                 ctx.initial_fbp(**kw)
+
+
+@pytest.mark.parametrize("n", [1, 63, 1025, 300_000])
+@pytest.mark.parametrize("nz,tau", [(1, 2.0), (4, 0.05), (3, 0.004)])
+def test_bins_in_any_order_of_the_histories(n, nz, tau):
+    """The bins of one angle collected per workgroup (few cells), one history
+    per lane (more cells than a workgroup's histories, or than the LDS holds):
+    the sums are whole numbers, so the image is the same bits whether the
+    histories come angle by angle or shuffled, and it is the oracle's to one
+    float32 rounding."""
+    w = synth.workload("vol64", n_hist=max(n, 1000))
+    h = {k: np.ascontiguousarray(v[:n]) for k, v in w.histories().items()}
+    g = synth.Grid(21, 17, nz, 1.0, 1.0, 2.5, -10.5, -8.5, -1.25 * nz)
+    img, _, want = fbp_both(w, h, 12, tau, 0, False, grid=g)
+    assert rel_err(img, want) <= 1e-6
+    order = np.random.default_rng(5).permutation(n)
+    major = np.argsort(np.arctan2(h["uy"], h["ux"]), kind="stable")
+    for o in (order, major):
+        hh = {k: np.ascontiguousarray(v[o]) for k, v in h.items()}
+        with tvs.Context(g, block_size=256, path_mode="otf") as ctx:
+            ctx.load_histories(hh)
+            assert np.array_equal(ctx.initial_fbp(12, median_radius=0, t_bin_mm=tau,
+                                                  clip_negative=False), img)
