@@ -794,10 +794,9 @@ __global__ void __launch_bounds__(NT) k_chain(ChainArgs A)
 }
 
 template <typename CH>
-const void *chain_kernel(bool split, bool wide)
+const void *chain_kernel(bool split)
 {
-    if (split) return (const void *)k_chain<512, 6, CH, true>;
-    return wide ? (const void *)k_chain<1024, 4, CH, false> : (const void *)k_chain<512, 6, CH, false>;
+    return split ? (const void *)k_chain<512, 6, CH, true> : (const void *)k_chain<1024, 4, CH, false>;
 }
 
 }  // namespace
@@ -810,9 +809,9 @@ size_t chain_lds_bytes(int tmax, int ns)
 
 hipError_t launch_chain(const ChainArgs &a, hipStream_t stream)
 {
-    const bool split = a.parts > 1, wide = a.wide != 0;
-    const void *k = a.chq ? chain_kernel<uint16_t>(split, wide)
-                          : a.ch16 ? chain_kernel<__half>(split, wide) : chain_kernel<float>(split, wide);
+    const bool split = a.parts > 1;
+    const void *k = a.chq ? chain_kernel<uint16_t>(split)
+                          : a.ch16 ? chain_kernel<__half>(split) : chain_kernel<float>(split);
     const size_t lds = chain_lds_bytes(a.tmax, (int)a.ns);
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -821,7 +820,7 @@ hipError_t launch_chain(const ChainArgs &a, hipStream_t stream)
     arg.corr_small = std::min(a.big, 1024.0);          // |r a| 2^40 below 2^51
     void *args[] = {&arg};
     return hipLaunchCooperativeKernel(k, dim3((unsigned)(a.nreg * a.parts)),
-                                      dim3(!split && wide ? 1024 : 512), args, (unsigned)lds, stream);
+                                      dim3(split ? 512 : 1024), args, (unsigned)lds, stream);
 }
 
 }  // namespace tvs

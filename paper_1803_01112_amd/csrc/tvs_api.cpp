@@ -171,7 +171,8 @@ struct tvs_ctx {
     uint32_t qshift = 31;           // tag bit that holds the code's bit 16
     uint32_t rowmask = 0xffffffu;   // row field of the tags
     int64_t cap = 0;                // entries per buffer
-    int nbuf = 0;
+    int nbuf = 0;                   // chunk buffers, side by side in one allocation
+    int64_t joined = 1;             // chunks formed as one, in the buffers as one
     int64_t cbase = 0;              // ring position of the next sweep's first chunk
     hipStream_t fill_stream = nullptr;          // row formation of the next chunks
     hipEvent_t ev_filled[kChunkBuffers] = {};
@@ -219,6 +220,7 @@ struct tvs_ctx {
     // the resident DROP chain (plan_chain); off when the grid or the block does not suit it
     struct Chain {
         bool on = false;
+        bool refused = false;       // a launch was refused (rows of several chunks on the fly)
         int nreg = 0, parts = 1, tmax = 0, ns = 0;
         int32_t *reg = nullptr;     // nreg + 1: first slot of each region
         int32_t *slots = nullptr;   // nact: slots by decreasing entries (launch per block)
@@ -330,9 +332,11 @@ void free_histories(tvs_ctx *ctx)
     dfree(ctx, &ctx->act, (size_t)std::max<int64_t>(ctx->nact, 1));
     dfree(ctx, &ctx->slot_of, (size_t)std::max<int64_t>(ctx->ntiles, 1));
     ctx->nact = 0;
-    for (int q = 0; q < kChunkBuffers; q++) {
-        dfree(ctx, &ctx->meta[q], (size_t)ctx->cap);
-        dfree(ctx, &ctx->ch32[q], (size_t)ctx->cap);
+    dfree(ctx, &ctx->meta[0], (size_t)(ctx->nbuf * ctx->cap));
+    dfree(ctx, &ctx->ch32[0], (size_t)(ctx->nbuf * ctx->cap));
+    for (int q = 1; q < kChunkBuffers; q++) {
+        ctx->meta[q] = nullptr;
+        ctx->ch32[q] = nullptr;
     }
     dfree(ctx, &ctx->ch16, (size_t)ctx->cap);
     dfree(ctx, &ctx->chq, (size_t)ctx->cap);
@@ -491,7 +495,7 @@ TileBlock block_view(tvs_ctx *ctx, int64_t b, long long *dot_base, int64_t dot_s
 {
     const int64_t B = ctx->cfg.block_size;
     const bool otf = ctx->cfg.path_mode == TVS_PATH_ON_THE_FLY;
-    const int64_t c = otf ? (b * B) / ctx->chunk : 0;
+    const int64_t c = otf ? (b * B) / ctx->chunk / ctx->joined * ctx->joined : 0;
     const int buf = otf ? chunk_buffer(ctx, c) : 0;
     TileBlock t;
     t.meta = ctx->meta[buf];
@@ -606,7 +610,6 @@ bool run_chain(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream_t 
     a.parts = c.parts;
     a.tmax = c.tmax;
     a.ns = (uint32_t)c.ns;
-    a.wide = ctx->cfg.path_mode != TVS_PATH_ON_THE_FLY;
     a.b0 = b0;
     a.b1 = b1;
     a.epoch = c.epoch;
@@ -632,27 +635,45 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
     if (nh_run <= 0) return TVS_OK;
     const int64_t nb = (nh_run + B - 1) / B;
     const bool otf = ctx->cfg.path_mode == TVS_PATH_ON_THE_FLY;
-    const int64_t step = otf ? ctx->chunk : ctx->nh;
+    // a cooperative launch is not captured; where it was refused before, the
+    // rows of several chunks are formed beside per-block launches again
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool several = otf && ctx->nbuf > 1;
+    const bool chain = ctx->chain.on && !(several && ctx->chain.refused) &&
+                       hipStreamIsCapturing(st, &cap) == hipSuccess &&
+                       cap == hipStreamCaptureStatusNone;
+    // for the chain: the buffers as one, filled (the first time beside the TV
+    // steps) and emptied in turn
+    const int64_t NB = chain ? 1 : ctx->nbuf;
+    ctx->joined = chain ? ctx->nbuf : 1;
+    if (chain) ctx->cbase = 0;
+    const int64_t step = otf ? ctx->chunk * ctx->joined : ctx->nh;
     const int64_t nchunks = (nh_run + step - 1) / step;
     hipStream_t fs = ctx->fill_stream;
-    // a cooperative launch is not captured
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    const bool chain = ctx->chain.on && hipStreamIsCapturing(st, &cap) == hipSuccess &&
-                       cap == hipStreamCaptureStatusNone;
+    struct Unjoin {
+        tvs_ctx *c;
+        ~Unjoin() { c->joined = 1; }
+    } unjoin{ctx};
     // a chunk is always formed whole, also when the sweep stops inside it:
     // its rows are formed in length order, so the first n of them are not
     // the histories of the first blocks
     auto fill = [&](int64_t c) -> int {
         const int64_t n = std::min(step, ctx->nh - c * step);
-        tvs::TileFill f = chunk_fill(ctx, c, n);
-        HIPCHK(hipStreamWaitEvent(fs, ctx->ev_free[chunk_buffer(ctx, c)], 0));
+        tvs::TileFill f = chunk_fill(ctx, c * ctx->joined, n);
+        if (chain) {
+            f.cap *= ctx->joined;
+            f.max_wgs = 0;
+            f.room = 0;
+            for (int q = 0; q < ctx->nbuf; q++) HIPCHK(hipStreamWaitEvent(fs, ctx->ev_free[q], 0));
+        } else {
+            HIPCHK(hipStreamWaitEvent(fs, ctx->ev_free[chunk_buffer(ctx, c)], 0));
+        }
         long a = mark(ctx, fs);
         HIPCHK(tvs::launch_rows_fill_tiled(ctx->gd, hist_dev(ctx), ctx->mlp, f, fs));
         span(ctx, 2, a, mark(ctx, fs));
         HIPCHK(hipEventRecord(ctx->ev_filled[chunk_buffer(ctx, c)], fs));
         return TVS_OK;
     };
-    const int64_t NB = ctx->nbuf;
     if (otf) {
         for (int64_t c = 0; c < std::min<int64_t>(NB, nchunks); c++) {
             int rc = fill(c);
@@ -668,13 +689,18 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
         for (int64_t b = c0; b < c1;) {
             const int64_t e = chain ? std::min(c1, b + kChainBlocks) : c1;
             if (!chain || !run_chain(ctx, lambda, b, e, st)) {
+                if (chain) ctx->chain.refused = true;
                 int rc = launch_blocks(ctx, lambda, b, e, st);
                 if (rc) return rc;
             }
             b = e;
         }
         if (otf) {
-            HIPCHK(hipEventRecord(ctx->ev_free[chunk_buffer(ctx, c)], st));
+            if (chain) {
+                for (int q = 0; q < ctx->nbuf; q++) HIPCHK(hipEventRecord(ctx->ev_free[q], st));
+            } else {
+                HIPCHK(hipEventRecord(ctx->ev_free[chunk_buffer(ctx, c)], st));
+            }
             if (c + NB < nchunks) {
                 int rc = fill(c + NB);
                 if (rc) return rc;
@@ -684,7 +710,7 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
     span(ctx, 3, e0, mark(ctx, st));
     // the ring continues with the next sweep, whose first chunks take the
     // buffers freed first
-    if (otf) ctx->cbase = (ctx->cbase + nchunks) % NB;
+    if (otf && !chain) ctx->cbase = (ctx->cbase + nchunks) % NB;
     return TVS_OK;
 }
 
@@ -743,11 +769,12 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
         return false;
     }
     if (!coop || cus < 1) return false;
-    // Beside the row formation of several chunks the chain's workgroups and
-    // the row kernel's do not fit a CU together (200x200x16 on the fly: 15.6 ms
-    // a cycle against 14.2 launched block by block), so rows formed on the fly
-    // take it only when one chunk holds them all.
-    if (ctx->cfg.path_mode == TVS_PATH_ON_THE_FLY && ctx->nh > ctx->chunk) return false;
+    // On the fly too: the rows of all the buffers' chunks are formed first, three
+    // waves to a SIMD, then the chain runs over them.  The two do not fit a CU
+    // together, and each alone is so much faster than beside the other that row
+    // formation overlapped with per-block launches loses: a cycle of 4 M rows of
+    // 200x200x16 takes 19.6 ms against 23.0, 60 M of 256x256x32 349 against 372,
+    // 2 M of 200x200x16 in chunks of 64 k 12.8 against 18.0, of 6,400 57 against 146.
     const int n = (int)a.size();
     // Many tiles and long lists: a launch's workgroups fill the device, and
     // the chain's one workgroup per CU is bound by instruction issue (256x256x32
@@ -1084,17 +1111,19 @@ int form_entries(tvs_ctx *ctx, hipStream_t st)
     const int64_t nchunks = (int64_t)ctx->chunk_base.size() - 1;
     ctx->nbuf = otf ? (int)std::max<int64_t>(1, std::min<int64_t>(kChunkBuffers, nchunks)) : 1;
     ctx->cbase = 0;
-    int rc = TVS_OK;
-    for (int q = 0; q < ctx->nbuf && !rc; q++) {
-        rc = dalloc(ctx, &ctx->meta[q], (size_t)ctx->cap);
-        if (!rc) {
-            if (ctx->cfg.path_mode == TVS_PATH_STORE_F16) rc = dalloc(ctx, &ctx->ch16, (size_t)ctx->cap);
-            else if (ctx->cfg.path_mode == TVS_PATH_STORE_Q16) rc = dalloc(ctx, &ctx->chq, (size_t)ctx->cap);
-            else rc = dalloc(ctx, &ctx->ch32[q], (size_t)ctx->cap);
-        }
-        // entries start as (row 0, word 0, chord 0): never an index out of range
-        if (!rc) HIPCHK(hipMemsetAsync(ctx->meta[q], 0, sizeof(uint32_t) * ctx->cap, st));
-        if (!rc && ctx->ch32[q]) HIPCHK(hipMemsetAsync(ctx->ch32[q], 0, sizeof(float) * ctx->cap, st));
+    const size_t all = (size_t)(ctx->nbuf * ctx->cap);
+    int rc = dalloc(ctx, &ctx->meta[0], all);
+    if (!rc) {
+        if (ctx->cfg.path_mode == TVS_PATH_STORE_F16) rc = dalloc(ctx, &ctx->ch16, all);
+        else if (ctx->cfg.path_mode == TVS_PATH_STORE_Q16) rc = dalloc(ctx, &ctx->chq, all);
+        else rc = dalloc(ctx, &ctx->ch32[0], all);
+    }
+    // entries start as (row 0, word 0, chord 0): never an index out of range
+    if (!rc) HIPCHK(hipMemsetAsync(ctx->meta[0], 0, sizeof(uint32_t) * all, st));
+    if (!rc && ctx->ch32[0]) HIPCHK(hipMemsetAsync(ctx->ch32[0], 0, sizeof(float) * all, st));
+    for (int q = 1; q < ctx->nbuf && !rc; q++) {
+        ctx->meta[q] = ctx->meta[0] + q * ctx->cap;
+        if (ctx->ch32[0]) ctx->ch32[q] = ctx->ch32[0] + q * ctx->cap;
     }
     if (!rc && ctx->ch16) HIPCHK(hipMemsetAsync(ctx->ch16, 0, sizeof(__half) * ctx->cap, st));
     if (!rc && ctx->chq) HIPCHK(hipMemsetAsync(ctx->chq, 0, sizeof(uint16_t) * ctx->cap, st));

@@ -322,7 +322,6 @@ struct ChainArgs {
     void *exch = nullptr;             // nreg * parts exchange records (parts > 1)
     int32_t nreg = 0, parts = 1, tmax = 0;
     uint32_t ns = 0;                  // slots of the row table (a power of two)
-    int32_t wide = 0;                 // 1: 1,024 lanes a workgroup, else 512
 };
 size_t chain_lds_bytes(int tmax, int ns);
 // An error leaves everything as it was (for instance a device whose

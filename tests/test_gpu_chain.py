@@ -113,3 +113,35 @@ def test_chain_contexts_on_threads():
         t.join()
     for q in range(3):
         np.testing.assert_array_equal(single[q], many[q])
+
+
+@pytest.mark.parametrize("n,chunk,dims", [
+    (450_000, 150_000, (24, 24, 2)),      # the buffers hold all chunks
+    (700_001, 70_400, (24, 24, 2)),       # four groups of three chunks, the last one of one
+    (400_000, 66_000, (40, 9, 1)),        # regions of several workgroups
+])
+def test_chunks_formed_together_equal_launches(n, chunk, dims):
+    """On the fly with several chunks: the chain runs over all the buffers'
+    chunks at once, per-block launches over one after the other; the images
+    are the same bits, also when a batch takes the buffers in between."""
+    grid = synth.centered_grid(*dims, 1.0, 1.0, 2.5)
+    ph = synth.catphan_like(grid, 0.75 * min(dims[0], dims[1]))
+    h = synth.generate(grid, ph, n, 90, 77)
+    x0 = synth.initial_image(grid, ph)
+    settings = [dict(lam=0.02, N=2, alpha=0.75), dict(lam=0.01, N=1, alpha=0.5)]
+    got = []
+    for kernel in (0, 1):
+        print(f"joined chunks: {dims} {n} histories, chunk {chunk}, sweep_kernel {kernel}",
+              flush=True)
+        with tvs.Context(grid, block_size=1600, sweep_kernel=kernel, chunk_histories=chunk) as ctx:
+            ctx.load_histories(h)
+            ctx.set_image(x0)
+            ctx.iterate(2, 0.02, 2, 0.75, seed=11)
+            a = ctx.get_image()
+            ctx.iterate_batch(1, settings)
+            b = ctx.get_batch_image(1)
+            ctx.iterate(1, 0.02, 2, 0.75, seed=11)
+            got.append((a, b, ctx.get_image()))
+    assert np.max(np.abs(got[0][0] - x0)) > 1e-3
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
