@@ -1061,6 +1061,87 @@ k_hull_decide(GridDev g, const uint32_t *in_cnt, const uint32_t *out_cnt, uint32
 }
 
 // dst[b] = src[b * stride] for b = 0 .. n - 1
+// Longest row and number of empty rows: stat[0], stat[1] (cleared before).
+__global__ void __launch_bounds__(kThreads) k_row_stats(const int32_t *nnz, int64_t n, uint32_t *stat)
+{
+    uint32_t mx = 0, empty = 0;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kThreads) {
+        const uint32_t len = (uint32_t)nnz[i];
+        mx = len > mx ? len : mx;
+        empty += len == 0u;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t m = (uint32_t)__shfl_xor((int)mx, o, 64);
+        mx = m > mx ? m : mx;
+        empty += (uint32_t)__shfl_xor((int)empty, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(stat, mx);
+        if (empty) atomicAdd(stat + 1, empty);
+    }
+}
+
+// Processing order of the row passes: within each DROP block, histories by
+// decreasing row length (a counting sort over at most BINS classes of
+// lengths), so that the lanes of a wavefront walk rows of similar length while
+// a block's tile lists are still written together (their partly written lines
+// meet in the L2 before they are evicted).  Each segment's place is fixed
+// otherwise, so the order changes no result, nor does that of rows of one class.
+// Two passes over the lengths (4 B a history) and one over the order; sorted on
+// the host, with the copies there and back, and with allocations made anew, a
+// request of 2 M histories of 128x128x8 took 31.8 ms, 25.6 now.
+template <int NT, int BINS>
+__global__ void __launch_bounds__(NT)
+k_row_order(const int32_t *nnz, int64_t n, int64_t B, int64_t nblocks,
+            const uint32_t *stat, int32_t *order)
+{
+    __shared__ uint32_t place[BINS], part[NT];
+    const int tid = threadIdx.x;
+    const uint32_t mx = stat[0];
+    // class of a length, the longest rows' lowest: (mx - len) scaled to the classes
+    const bool exact = mx < (uint32_t)BINS;
+    const float scale = (float)(BINS - 1) / (float)(mx > 0 ? mx : 1u);
+    auto bin = [&](int32_t len) {
+        const uint32_t d = mx - (uint32_t)len;
+        if (exact) return (int)d;
+        const int b = (int)((float)d * scale);
+        return b < BINS ? b : BINS - 1;
+    };
+    const int per = BINS / NT;
+    for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        const int64_t f0 = b * B, f1 = f0 + B < n ? f0 + B : n;
+        for (int q = tid; q < BINS; q += NT) place[q] = 0;
+        __syncthreads();
+#pragma unroll 4
+        for (int64_t i = f0 + tid; i < f1; i += NT) atomicAdd(place + bin(nnz[i]), 1u);
+        __syncthreads();
+        // exclusive sums: each thread its `per` classes, then the threads' totals
+        uint32_t sum = 0;
+        for (int q = 0; q < per; q++) sum += place[tid * per + q];
+        part[tid] = sum;
+        __syncthreads();
+        for (int o = 1; o < NT; o <<= 1) {
+            const uint32_t v = tid >= o ? part[tid - o] : 0u;
+            __syncthreads();
+            part[tid] += v;
+            __syncthreads();
+        }
+        uint32_t pos = part[tid] - sum;
+        for (int q = 0; q < per; q++) {
+            const uint32_t c = place[tid * per + q];
+            place[tid * per + q] = pos;
+            pos += c;
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int64_t i = f0 + tid; i < f1; i += NT)
+            order[f0 + (int64_t)atomicAdd(place + bin(nnz[i]), 1u)] = (int32_t)i;
+        __syncthreads();
+    }
+}
+
 __global__ void __launch_bounds__(kThreads)
 k_pick(const int64_t *src, int64_t stride, int64_t n, int64_t *dst)
 {
@@ -1267,6 +1348,29 @@ hipError_t launch_hull_decide(const GridDev &g, const uint32_t *in_cnt, const ui
     if (wgs > 4096) wgs = 4096;
     hipLaunchKernelGGL(k_hull_decide, dim3((unsigned)wgs), dim3(kThreads), 0, stream, g, in_cnt,
                        out_cnt, min_in, max_out, hull, mask);
+    return hipGetLastError();
+}
+
+hipError_t launch_row_stats(const int32_t *nnz, int64_t n, uint32_t *stat, hipStream_t stream)
+{
+    if (n <= 0) return hipSuccess;
+    const int64_t wgs = std::min<int64_t>((n + kThreads - 1) / kThreads, 1024);
+    hipLaunchKernelGGL(k_row_stats, dim3((unsigned)wgs), dim3(kThreads), 0, stream, nnz, n, stat);
+    return hipGetLastError();
+}
+
+hipError_t launch_row_order(const int32_t *nnz, int64_t n, int64_t B, const uint32_t *stat,
+                            int32_t *order, hipStream_t stream)
+{
+    if (n <= 0) return hipSuccess;
+    const int64_t nblocks = (n + B - 1) / B;
+    const dim3 grid((unsigned)std::min<int64_t>(nblocks, 1 << 16));
+    if (B < 1024)       // fewer classes to clear and add up
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_row_order<256, 256>), grid, dim3(256), 0, stream, nnz, n,
+                           B, nblocks, stat, order);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_row_order<1024, 4096>), grid, dim3(1024), 0, stream, nnz,
+                           n, B, nblocks, stat, order);
     return hipGetLastError();
 }
 

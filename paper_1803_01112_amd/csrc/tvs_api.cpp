@@ -130,6 +130,10 @@ struct tvs_ctx {
     int cus = 256;
     uint64_t budget = 0;
     uint64_t bytes = 0;
+    // during tvs_load_histories: allocations given back in that call, for its next ones
+    bool recycle = false;
+    uint64_t spare_bytes = 0;
+    std::vector<std::pair<void *, size_t>> spare;
     std::string err;
 
     // image side (float64, tiled layout)
@@ -269,11 +273,29 @@ int fail(tvs_ctx *ctx, int code, const std::string &msg)
 
 void chain_release(tvs_ctx *ctx);
 
+// Frees what tvs_load_histories has given back and not taken again.
+void drop_spare(tvs_ctx *ctx)
+{
+    for (auto &s : ctx->spare) (void)hipFree(s.first);
+    ctx->spare.clear();
+    ctx->spare_bytes = 0;
+}
+
 template <typename T>
 int dalloc(tvs_ctx *ctx, T **p, size_t count)
 {
     size_t bytes = count * sizeof(T);
     if (bytes == 0) bytes = sizeof(T);
+    for (size_t i = 0; i < ctx->spare.size(); i++) {
+        if (ctx->spare[i].second != bytes) continue;
+        if (ctx->bytes + bytes > ctx->budget) break;
+        *p = static_cast<T *>(ctx->spare[i].first);
+        ctx->spare.erase(ctx->spare.begin() + (long)i);
+        ctx->spare_bytes -= bytes;
+        ctx->bytes += bytes;
+        return TVS_OK;
+    }
+    if (ctx->bytes + ctx->spare_bytes + bytes > ctx->budget) drop_spare(ctx);
     // the chain's small workspace gives way to whatever else needs the room
     if (ctx->bytes + bytes > ctx->budget) chain_release(ctx);
     if (ctx->bytes + bytes > ctx->budget)
@@ -282,6 +304,11 @@ int dalloc(tvs_ctx *ctx, T **p, size_t count)
                         std::to_string(ctx->budget) + " B");
     void *q = nullptr;
     hipError_t e = hipMalloc(&q, bytes);
+    if (e != hipSuccess && !ctx->spare.empty()) {
+        (void)hipGetLastError();
+        drop_spare(ctx);
+        e = hipMalloc(&q, bytes);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(ctx, TVS_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
@@ -295,9 +322,14 @@ template <typename T>
 void dfree(tvs_ctx *ctx, T **p, size_t count)
 {
     if (*p) {
-        (void)hipFree(*p);
         size_t bytes = count * sizeof(T);
         if (bytes == 0) bytes = sizeof(T);
+        if (ctx->recycle) {
+            ctx->spare.emplace_back(*p, bytes);
+            ctx->spare_bytes += bytes;
+        } else {
+            (void)hipFree(*p);
+        }
         ctx->bytes -= std::min<uint64_t>(ctx->bytes, bytes);
         *p = nullptr;
     }
@@ -935,8 +967,9 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
     uint32_t *btc = nullptr, *sbc = nullptr;   // list lengths by (block, tile), by (block, slot)
     int64_t nsbc = 0;
     int64_t *tmp = nullptr;
-    // scan scratch, later also the gathered block starts
-    const int64_t ntmp = std::max(tvs::scan_tmp_elems(std::max(n, nbt)) + 1, (n + B - 1) / B + 1);
+    // scan scratch, also the gathered block starts and, behind them, the row statistics
+    const int64_t nblocks = (n + B - 1) / B;
+    const int64_t ntmp = std::max(tvs::scan_tmp_elems(std::max(n, nbt)) + 1, nblocks + 2);
     auto cleanup = [&]() {
         dfree(ctx, &cnt, (size_t)std::max<int64_t>(n, 1));
         dfree(ctx, &cseg, (size_t)std::max<int64_t>(n, 1));
@@ -955,13 +988,31 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
     hipError_t e = tvs::launch_rows_count(ctx->gd, hd, ctx->mlp, 0, n, cnt, cseg, st);
     if (e == hipSuccess) e = tvs::launch_scan(cnt, n, ctx->row_off, tmp, st);
     if (e == hipSuccess) e = tvs::launch_scan(cseg, n, ctx->seg_off, tmp, st);
-    std::vector<int64_t> off((size_t)n + 1);
+    // first entry of every block (and the end), segments, longest and empty rows
+    std::vector<int64_t> off((size_t)nblocks + 1);
     int64_t nseg = 0;
+    uint32_t stat[2] = {0, 0};
+    uint32_t *dstat = reinterpret_cast<uint32_t *>(tmp + nblocks + 1);
+    if (e == hipSuccess) e = hipMemsetAsync(dstat, 0, sizeof(stat), st);
+    if (e == hipSuccess) e = tvs::launch_row_stats(cnt, n, dstat, st);
+    if (e == hipSuccess && nblocks > 0) {
+        e = tvs::launch_pick(ctx->row_off, B, nblocks, tmp, st);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(off.data(), tmp, sizeof(int64_t) * nblocks, hipMemcpyDeviceToHost, st);
+    }
     if (e == hipSuccess)
-        e = hipMemcpyAsync(off.data(), ctx->row_off, sizeof(int64_t) * (n + 1),
+        e = hipMemcpyAsync(&off[(size_t)nblocks], ctx->row_off + n, sizeof(int64_t),
                            hipMemcpyDeviceToHost, st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(&nseg, ctx->seg_off + n, sizeof(int64_t), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(stat, dstat, sizeof(stat), hipMemcpyDeviceToHost, st);
+    rc = dalloc(ctx, &ctx->order, (size_t)n);
+    if (rc) {
+        (void)hipStreamSynchronize(st);
+        cleanup();
+        return rc;
+    }
+    if (e == hipSuccess) e = tvs::launch_row_order(cnt, n, B, dstat, ctx->order, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         cleanup();
@@ -969,18 +1020,13 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
     }
     dfree(ctx, &cnt, (size_t)std::max<int64_t>(n, 1));
     dfree(ctx, &cseg, (size_t)std::max<int64_t>(n, 1));
-    const int64_t total = off[(size_t)n];
-    int64_t mx = 0, sk = 0;
-    for (int64_t i = 0; i < n; i++) {
-        const int64_t len = off[(size_t)i + 1] - off[(size_t)i];
-        mx = std::max(mx, len);
-        sk += (len == 0);
-    }
+    const int64_t total = off[(size_t)nblocks];
+    const int64_t mx = stat[0], sk = stat[1];
     ctx->nnz = total;
     ctx->max_row = mx;
     ctx->skipped = sk;
     ctx->nseg = nseg;
-    ctx->nblocks = (n + B - 1) / B;
+    ctx->nblocks = nblocks;
     int64_t chunk = ctx->cfg.chunk_histories;
     if (chunk <= 0) {
         // about 2^20 histories, as even as whole blocks allow: the row
@@ -995,42 +1041,9 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
         chunk = (chunk + B - 1) / B * B;
     }
     ctx->chunk = std::max<int64_t>(chunk, 1);
-    for (int64_t f = 0; f < n; f += ctx->chunk) ctx->chunk_base.push_back(off[(size_t)f]);
+    for (int64_t f = 0; f < n; f += ctx->chunk)
+        ctx->chunk_base.push_back(off[(size_t)(f / B)]);
     ctx->chunk_base.push_back(total);
-    // processing order of the row passes: within each DROP block, histories
-    // by decreasing row length (a counting sort), so that the lanes of a
-    // wavefront walk rows of similar length while a block's tile lists are
-    // still written together (their partly written lines meet in the L2
-    // before they are evicted); blocks never straddle a chunk.  Each
-    // segment's place is fixed below, so the order changes no result
-    {
-        std::vector<int32_t> ord((size_t)n);
-        std::vector<int64_t> cnt_len((size_t)mx + 2);
-        for (int64_t f0 = 0; f0 < n; f0 += B) {
-            const int64_t f1 = std::min(n, f0 + B);
-            std::fill(cnt_len.begin(), cnt_len.end(), 0);
-            for (int64_t i = f0; i < f1; i++) cnt_len[(size_t)(mx - (off[(size_t)i + 1] - off[(size_t)i]))]++;
-            int64_t pos = f0;
-            for (size_t q = 0; q < cnt_len.size(); q++) {
-                const int64_t c0 = cnt_len[q];
-                cnt_len[q] = pos;
-                pos += c0;
-            }
-            for (int64_t i = f0; i < f1; i++)
-                ord[(size_t)cnt_len[(size_t)(mx - (off[(size_t)i + 1] - off[(size_t)i]))]++] = (int32_t)i;
-        }
-        rc = dalloc(ctx, &ctx->order, (size_t)n);
-        if (rc) {
-            cleanup();
-            return rc;
-        }
-        e = hipMemcpyAsync(ctx->order, ord.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) {
-            cleanup();
-            return fail(ctx, TVS_EDEVICE, std::string("row order: ") + hipGetErrorString(e));
-        }
-    }
     // integer ranges of the DROP sums: no voxel takes more than 2B entries of
     // one block, no row more than max_row entries
     ctx->big = 2097152.0 / (double)B;                              // 2^21 / B
@@ -1087,7 +1100,7 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
         return fail(ctx, TVS_EDEVICE, "tile lists: a row walk disagreed with the count pass");
     std::memcpy(&ctx->chord_max, &fl[kFlagChordMax], sizeof(float));
     for (int64_t b = 0; b <= ctx->nblocks && ctx->nblocks > 0; b++) {
-        const int64_t want = (b < ctx->nblocks) ? off[(size_t)(b * B)] : total;
+        const int64_t want = off[(size_t)b];
         if (starts[(size_t)b] != want)
             return fail(ctx, TVS_EDEVICE,
                         "tile lists disagree with the row lengths at block " + std::to_string(b) +
@@ -1403,6 +1416,20 @@ int tvs_load_histories(tvs_ctx *ctx, int64_t n, const tvs_histories *h, int on_d
     HIPCHK(hipStreamSynchronize(st));
     HIPCHK(hipStreamSynchronize(ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->fill_stream));
+    // Allocations given back in this call serve its next ones of the same size
+    // (a new scan of the same shape, and the temporaries: an
+    // allocation and its release take 0.1 to 0.4 ms) and are freed at its end.  Work of any stream on the old ones ends first, as
+    // hipFree would have seen to.
+    if (ctx->hist) HIPCHK(hipDeviceSynchronize());
+    struct Recycle {
+        tvs_ctx *c;
+        ~Recycle()
+        {
+            c->recycle = false;
+            drop_spare(c);
+        }
+    } recycle{ctx};
+    ctx->recycle = true;
     free_histories(ctx);
     reset_state(ctx);
     HIPCHK(hipMemsetAsync(ctx->x, 0, sizeof(double) * ctx->nvox, st));

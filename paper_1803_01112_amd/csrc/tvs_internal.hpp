@@ -219,6 +219,11 @@ hipError_t launch_median(const GridDev &g, const double *x, int radius, float *o
                          hipStream_t stream);
 // cos and sin of the A beam angles a * 2 pi / A into cs (2 A doubles).
 hipError_t launch_fbp_angles(int32_t A, double *cs, hipStream_t stream);
+// Longest row and number of empty rows into stat[0], stat[1] (cleared before).
+hipError_t launch_row_stats(const int32_t *nnz, int64_t n, uint32_t *stat, hipStream_t stream);
+// Histories of each DROP block by decreasing row length (stat as above).
+hipError_t launch_row_order(const int32_t *nnz, int64_t n, int64_t B, const uint32_t *stat,
+                            int32_t *order, hipStream_t stream);
 hipError_t launch_pick(const int64_t *src, int64_t stride, int64_t n, int64_t *dst,
                        hipStream_t stream);
 // Fills the entry-side table of m for depths j = 0 .. nj - 1 (3 doubles each).
