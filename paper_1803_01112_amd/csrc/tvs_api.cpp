@@ -99,6 +99,12 @@ void *g_scratch_ptr[kMaxDevices] = {};
 hipError_t g_scratch_status[kMaxDevices] = {};
 bool g_scratch_done[kMaxDevices] = {};
 
+// Resident chains of one device run one after the other: each launch waits for
+// the event that the last one of any context recorded.  Two of them at once
+// could each hold part of the CUs and wait for the rest.
+std::mutex g_chain_mu;
+hipEvent_t g_chain_done[kMaxDevices] = {};
+
 // Looks up this device's copy of `scratch` (the device must be current).
 void fbp_scratch_setup(int dev)
 {
@@ -647,10 +653,21 @@ bool run_chain(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream_t 
     a.epoch = c.epoch;
     a.sub_epoch = c.sub_epoch;
     const bool timed = ctx->cfg.time_sample > 0;
+    const int dev = ctx->cfg.device;
+    if (dev < 0 || dev >= kMaxDevices) return false;
     const long e0 = timed ? mark(ctx, st) : -1;
-    if (tvs::launch_chain(a, st) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
+    {
+        std::lock_guard<std::mutex> lk(g_chain_mu);
+        hipEvent_t &done = g_chain_done[dev];
+        hipError_t e = done ? hipStreamWaitEvent(st, done, 0)
+                            : hipEventCreateWithFlags(&done, hipEventDisableTiming);
+        if (e == hipSuccess) e = tvs::launch_chain(a, st);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        e = hipEventRecord(done, st);
+        if (e != hipSuccess) (void)hipStreamSynchronize(st);
     }
     if (timed) span(ctx, 4, e0, mark(ctx, st), b1 - b0);
     c.epoch += (uint32_t)(b1 - b0) + 1u;
