@@ -61,7 +61,9 @@ k_tvb_grad(GridDev G, const double *x, int S, int V, uint32_t active, const doub
         vcoord(G, p, i, j, k);
         if (!(i < nx && j < ny && ((active >> s) & 1u))) continue;
         const double e2 = eps[s] * eps[s];
-        auto X = [&](int64_t di, int64_t dj) { return x[vaddr(G, i + di, j + dj, k) * at.step]; };
+        auto X = [&](int32_t di, int32_t dj) {
+            return x[(int64_t)vaddr32(G, (int32_t)i + di, (int32_t)j + dj, (int32_t)k) * at.step];
+        };
         auto dxf = [&](int64_t ii, int64_t jj) {
             return (i + ii + 1 < nx) ? X(ii + 1, jj) - X(ii, jj) : 0.0;
         };
@@ -99,15 +101,20 @@ k_tvb_grad(GridDev G, const double *x, int S, int V, uint32_t active, const doub
 // those of every V-th workgroup of the gradient, then the V sums in order.  A
 // launch of its own: handing the partials over inside the gradient's launch
 // made its workgroups write back the L2's dirty lines (300 us a gradient of 24
-// settings of 200x200x16 against 248 and 3 for this launch).
+// settings of 200x200x16 against 206 and 7 for this launch; 248 with 64-bit
+// voxel coordinates, 30 without the sums' loads in flight together).
 __global__ void __launch_bounds__(kThreads)
 k_tvb_norm(const double *part, uint32_t n, int S, int V, double *norm2)
 {
     __shared__ double red[kThreads];
     const int v = threadIdx.x, s = blockIdx.x;
     double a = 0.0;
-    if (v < V)
-        for (uint32_t w = v; w < n; w += V) a += part[(int64_t)w * S + s];
+    if (v < V) {
+        const double *p = part + (int64_t)v * S + s;
+        const int terms = ((int)n - v + V - 1) / V, step = V * S;
+#pragma unroll 16
+        for (int q = 0; q < terms; q++) a += p[q * step];
+    }
     red[v] = a;
     __syncthreads();
     if (v == 0) {

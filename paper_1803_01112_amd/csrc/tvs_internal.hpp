@@ -51,16 +51,18 @@ __host__ __device__ inline int32_t vaddr32(const GridDev &g, int32_t i, int32_t 
     return (tile << kTileShift) | in;
 }
 
-// Inverse of vaddr: voxel coordinates of tiled-layout word a.
+// Inverse of vaddr: voxel coordinates of tiled-layout word a (of an image of
+// fewer than 2^31 words, as above: 32-bit quotients).
 __host__ __device__ inline void vcoord(const GridDev &g, int64_t a, int64_t &i, int64_t &j,
                                        int64_t &k)
 {
-    const int64_t tile = a >> kTileShift, in = a & (kTileWords - 1);
-    const int64_t brick = in >> 3, w = in & 7;
-    const int64_t t2 = tile / g.ntx;
-    const int64_t tx = tile - t2 * g.ntx;
-    k = t2 / g.nty;
-    const int64_t ty = t2 - k * g.nty;
+    const uint32_t tile = (uint32_t)(a >> kTileShift), in = (uint32_t)a & (kTileWords - 1);
+    const uint32_t brick = in >> 3, w = in & 7;
+    const uint32_t t2 = tile / (uint32_t)g.ntx;
+    const uint32_t tx = tile - t2 * (uint32_t)g.ntx;
+    const uint32_t z = t2 / (uint32_t)g.nty;
+    const uint32_t ty = t2 - z * (uint32_t)g.nty;
+    k = z;
     i = tx * kTileSide + (brick & 3) * 4 + (w & 3);
     j = ty * kTileSide + (brick >> 2) * 2 + (w >> 2);
 }
