@@ -64,6 +64,8 @@ def sweep_bytes(H, nnz, mode):
 KERNEL_SOURCES = {
     "k_drop_tile": ("paper_1803_01112_amd/csrc/drop.hip", "paper_1803_01112_amd/csrc/device_common.hpp",
                     "paper_1803_01112_amd/csrc/tvs_internal.hpp"),
+    "k_chain": ("paper_1803_01112_amd/csrc/chain.hip", "paper_1803_01112_amd/csrc/device_common.hpp",
+                "paper_1803_01112_amd/csrc/tvs_internal.hpp"),
     "k_rows_fill_tiled": ("paper_1803_01112_amd/csrc/rows.hip", "paper_1803_01112_amd/csrc/tvs_internal.hpp"),
 }
 
@@ -528,9 +530,9 @@ def main():
                         args.latency_cycles)
     log(f"{args.path_mode}: {head}")
 
-    # dominant kernel of the timed region: the DROP step (one launch per
-    # block, kernel-stamped events on every k-th block) or the row formation
-    # on the second stream (events around every launch)
+    # dominant kernel of the timed region: the DROP chain (launches of many
+    # blocks, events around each; or one launch per block, kernel-stamped
+    # events on every k-th) or the row formation (events around every launch)
     nnz = st["nnz"]
     k1_ms = st["k1_ms_total"] / max(st["k_samples"], 1)
     if st["k_samples"] == 0:
@@ -538,7 +540,11 @@ def main():
         # time per step stands in for the launch duration
         k1_ms = st["drop_ms_total"] / max(st["drop_launches"], 1) / (T + 1)
     rows_ms = st["rows_ms_total"] / max(st["rows_launches"], 1)
-    per_cycle = {"k_drop_tile": k1_ms * (T + 1)}
+    # the resident chain times every block (events around launches of many),
+    # one launch per block every k-th; its time stands for a block's
+    chained = st["k_samples"] > max(st["drop_launches"], 1) * T // 2 and args.time_sample > 2
+    drop = "k_chain" if chained else "k_drop_tile"
+    per_cycle = {drop: k1_ms * (T if chained else T + 1)}
     if args.path_mode == "otf":
         per_cycle["k_rows_fill_tiled"] = st["rows_ms_total"] / max(st["cycles_timed"], 1)
     dom = max(per_cycle, key=per_cycle.get)
@@ -565,8 +571,7 @@ def main():
 
     roof = roofline_of(dom)
     roof["per_cycle_ms"] = per_cycle
-    # the other kernel of the cycle (on the fly the row formation runs beside
-    # the chain on its own stream)
+    # the other kernel of the cycle
     others = {k: roofline_of(k) for k in per_cycle if k != dom}
 
     forms = {}

@@ -104,7 +104,7 @@ typedef struct {
     int32_t fill_wgs_per_cu; /* on-the-fly rows: cap on the workgroups per compute unit of
                                 the row formation that runs beside the DROP chain; 0 or < 0:
                                 no cap */
-    int32_t fill_wide_pct;   /* on-the-fly rows: percentage of the chunks formed at the row
+    int32_t fill_wide_pct;   /* on-the-fly rows beside one launch per DROP block: percentage of the chunks formed at the row
                                 kernel's full occupancy (three waves per SIMD, which leaves a
                                 SIMD no room for DROP waves); the others are held at two
                                 waves per SIMD, with room for four DROP waves beside them;

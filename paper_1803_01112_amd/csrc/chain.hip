@@ -41,9 +41,9 @@
 // preparing the next block and 1.0 more at the barrier.  Other blocks of
 // 3200: 6.7 against 13.0 us at 128x128x8, 10.5 against 100 at 64x64.
 //
-// The launch is cooperative (all workgroups resident, no two such kernels
-// interleaved on a device); every wait is bounded and ends the kernel with an
-// error flag.
+// The launch is cooperative (all workgroups resident), and the library lets
+// the chains of several contexts follow one another; every wait is bounded and
+// ends the kernel with an error flag.
 #include <algorithm>
 #include <type_traits>
 
@@ -793,6 +793,10 @@ __global__ void __launch_bounds__(NT) k_chain(ChainArgs A)
     c.run();
 }
 
+// A region of its own takes 1,024 lanes of 4 entries: 7.2 us a block against 7.4
+// to 7.8 with 512 lanes of 6 (200x200x16, float32 store), 11.3 against 11.7 ms a
+// cycle of 2 M rows on the fly.  A shared region is divided so that each of its
+// workgroups has about two entries a lane of 512 (plan_chain).
 template <typename CH>
 const void *chain_kernel(bool split)
 {

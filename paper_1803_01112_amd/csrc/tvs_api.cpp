@@ -571,7 +571,7 @@ tvs::TileFill chunk_fill(tvs_ctx *ctx, int64_t c, int64_t n)
     f.err = ctx->flags + kFlagLists;
     f.max_wgs = ctx->fill_wgs;
     f.order = ctx->order;
-    // beside the DROP chain: chunk c at full occupancy when the running count
+    // beside per-block launches: chunk c at full occupancy when the running count
     // of such chunks steps up at c (fill_wide_pct of them, spread evenly),
     // else held at two waves per SIMD
     const int64_t pct = ctx->fill_wide_pct;
@@ -1046,10 +1046,10 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
     ctx->nblocks = nblocks;
     int64_t chunk = ctx->cfg.chunk_histories;
     if (chunk <= 0) {
-        // about 2^20 histories, as even as whole blocks allow: the row
-        // formation of the next sweep's first chunk waits for the DROP chain
-        // to leave that chunk's buffer, i.e. to finish the next-to-last chunk,
-        // so a small last chunk would leave the formation stream idle
+        // about 2^20 histories, as even as whole blocks allow: beside per-block
+        // launches the row formation of the next sweep's first chunk waits for
+        // them to leave that chunk's buffer, i.e. to finish the next-to-last
+        // chunk, so a small last chunk would leave the formation stream idle
         const int64_t target = std::max<int64_t>(B, ((int64_t)1 << 20) / B * B);
         const int64_t parts = std::max<int64_t>(1, (n + target - 1) / target);
         chunk = ((n + parts - 1) / parts + B - 1) / B * B;
@@ -1339,7 +1339,7 @@ int tvs_create(const tvs_grid *grid, const tvs_config *cfg_in, tvs_ctx **out)
         // tvs_autotune times the shares on the loaded histories)
         ctx->fill_wide_pct = cfg.fill_wide_pct < 0 ? 40 : std::min(cfg.fill_wide_pct, 100);
         // Tile workgroup size: 128 lanes on the fly (they leave the row
-        // formation beside the DROP chain more room) and for grids of more
+        // formation beside them more room) and for grids of more
         // tiles than twice the 256-lane workgroups the device holds at once
         // (8 per CU: fewer rounds of workgroups per step); else 256 lanes,
         // with which a step of a path store is shortest
@@ -2415,7 +2415,7 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
     }
     ctx->threads = out->tile_threads;
     ctx->split = out->sweep_kernel == 2 ? 1 : 0;
-    // on the fly: whole sweeps (the row formation beside the chain) for the
+    // on the fly: whole sweeps (the row formation beside the launches) for the
     // share of chunks formed at the row kernel's full occupancy; with one
     // chunk the share does not matter
     const int64_t nchunks = (ctx->nh + ctx->chunk - 1) / ctx->chunk;
