@@ -2357,8 +2357,13 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
     HIPCHK(hipMemcpyAsync(saved, ctx->x, sizeof(double) * ctx->nvox, hipMemcpyDeviceToDevice, st));
     const int ths[3] = {64, 128, 256};
     const int old_threads = ctx->threads, old_split = ctx->split;
-    // the candidates are launches per block; the chain goes on where it fits
-    const bool chain = ctx->chain.on;
+    // the candidates are launches per block, the shares those of chunks formed
+    // beside them (batches use both too); the chain goes on where it fits
+    struct ChainOff {
+        tvs_ctx *c;
+        bool on;
+        ~ChainOff() { c->chain.on = on && c->chain.reg; }
+    } chain_off{ctx, ctx->chain.on};
     ctx->chain.on = false;
     double best = 1e300;
     int nc = 0;
@@ -2403,7 +2408,6 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
         }
     }
     out->n_candidates = nc;
-    ctx->chain.on = chain && ctx->chain.reg;
     if (rc || best == 1e300) {
         dfree(ctx, &saved, (size_t)ctx->nvox);
         ctx->tev_used = 0;
