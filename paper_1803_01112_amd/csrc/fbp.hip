@@ -34,7 +34,7 @@ constexpr double kFixed = 4294967296.0;   // 2^32
 
 // The bin of a history's straight line: angle a and cell (slice, lateral bin).
 __device__ inline bool bin_of(const GridDev &g, const HistDev &H, int64_t i, int32_t A, double tau,
-                              int32_t nt, int32_t &a, int32_t &cell)
+                              int32_t nt, int32_t &a, int64_t &cell)
 {
     const double ex = H.s(kEx)[i], ey = H.s(kEy)[i], ez = H.s(kEz)[i];
     const double qx = H.s(kQx)[i], qy = H.s(kQy)[i], qz = H.s(kQz)[i];
@@ -59,7 +59,7 @@ __device__ inline bool bin_of(const GridDev &g, const HistDev &H, int64_t i, int
     const double kk = floor((vc - g.oz) / g.vz);
     if (!(kk >= 0.0 && kk < (double)g.nz)) return false;
     a = (int32_t)an;
-    cell = (int32_t)kk * nt + (int32_t)mm;
+    cell = (int64_t)kk * nt + (int64_t)mm;
     return true;
 }
 
@@ -103,7 +103,8 @@ k_fbp_bin(GridDev g, HistDev H, int64_t n, int64_t per, int32_t A, double tau, i
             wcnt[q] = 0;
         }
         if (tid < 64) {
-            int32_t a = -1, cell = 0;
+            int32_t a = -1;
+            int64_t cell = 0;
             const int64_t i = c0 + (c1 - c0) * tid / 64;
             const unsigned long long ok = __ballot(bin_of(g, H, i, A, tau, nt, a, cell));
             const unsigned long long late = ok >> 32;
@@ -117,7 +118,8 @@ k_fbp_bin(GridDev g, HistDev H, int64_t n, int64_t per, int32_t A, double tau, i
     const int32_t a0 = WIN ? angle : -1;
     for (int64_t base = c0; base < c1; base += kBinThreads) {
         const int64_t i = base + tid;
-        int32_t a = -1, cell = 0;
+        int32_t a = -1;
+        int64_t cell = 0;
         bool on = i < c1 && bin_of(g, H, i, A, tau, nt, a, cell);
         const long long v = on ? llrint((double)H.s(kWepl)[i] * kFixed) : 0;
         if (WIN && on && a == a0) {
