@@ -40,6 +40,11 @@ constexpr int64_t kDevLogCap = 4096;
 // formation stream can form the next sweep's first chunk while the DROP
 // chain still reads the last two of this sweep.
 constexpr int kChunkBuffers = 3;
+// Blocks from which a tile's lists keep 256 lanes busy for several rounds, so that
+// fewer rounds of workgroups no longer pay (two cycles of 4 M rows of 256x256x32 in a
+// 6-byte store with 128 / 256 lanes: 21.26 / 21.31 ms at B = 6,400, 17.00 / 16.25 at
+// 12,800, 13.88 / 13.20 at 25,600, 12.25 / 11.50 at 51,200)
+constexpr int32_t kLongBlock = 8192;
 
 // Blocks one launch of the resident chain takes at most (about 6 ms; a
 // launch's own cost is some 20 us).
@@ -827,7 +832,7 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
     const int n = (int)a.size();
     // Many tiles and long lists: a launch's workgroups fill the device, and
     // the chain's one workgroup per CU is bound by instruction issue (256x256x32
-    // at B = 25,600, 20,000 entries a CU: 44 us a block against 42 launched).
+    // at B = 25,600, 20,000 entries a CU: 44 us a block against 40 launched).
     // Shorter lists or fewer tiles are the chain's (2,000 entries a CU: 7.2
     // against 8.8 us).
     const double avg = (double)ctx->nnz / (double)std::max<int64_t>(ctx->nblocks, 1);
@@ -1339,12 +1344,13 @@ int tvs_create(const tvs_grid *grid, const tvs_config *cfg_in, tvs_ctx **out)
         // tvs_autotune times the shares on the loaded histories)
         ctx->fill_wide_pct = cfg.fill_wide_pct < 0 ? 40 : std::min(cfg.fill_wide_pct, 100);
         // Tile workgroup size: 128 lanes on the fly (they leave the row
-        // formation beside them more room) and for grids of more
+        // formation beside them more room) and for short blocks on grids of more
         // tiles than twice the 256-lane workgroups the device holds at once
         // (8 per CU: fewer rounds of workgroups per step); else 256 lanes,
         // with which a step of a path store is shortest
         const int64_t resident256 = 8 * (int64_t)(cus > 0 ? cus : 256);
-        const bool small = cfg.path_mode == TVS_PATH_ON_THE_FLY || ctx->ntiles > 2 * resident256;
+        const bool small = cfg.path_mode == TVS_PATH_ON_THE_FLY ||
+                           (ctx->ntiles > 2 * resident256 && cfg.block_size < kLongBlock);
         ctx->threads = cfg.tile_threads ? cfg.tile_threads : (small ? 128 : 256);
     }
 
