@@ -170,8 +170,9 @@ struct tvs_ctx {
     uint64_t *segtab = nullptr;     // nseg: global entry index of each segment's first entry
     int64_t nseg = 0;
     int64_t *bt_off = nullptr;      // nblocks * nact + 1 list starts, slots in order per block
-    int32_t *act = nullptr;         // tiles that some block's lists cross (slot -> tile)
+    int32_t *act = nullptr;         // tiles that some block's lists cross, the busiest first
     int32_t *slot_of = nullptr;     // ntiles: tile -> slot, -1 for a tile no list crosses
+    bool by_region = false;         // slots in the chain's order (else slot i is tile act[i])
     int64_t nact = 0;
     int64_t nblocks = 0;
     // entries: the store, or a ring of chunk buffers on the fly
@@ -238,7 +239,7 @@ struct tvs_ctx {
         bool refused = false;       // a launch was refused (rows of several chunks on the fly)
         int nreg = 0, parts = 1, tmax = 0, ns = 0;
         int32_t *reg = nullptr;     // nreg + 1: first slot of each region
-        int32_t *slots = nullptr;   // nact: slots by decreasing entries (launch per block)
+        int32_t *act = nullptr;     // nact: slot -> tile
         uint32_t *bar = nullptr;    // barrier counters: all workgroups', then one per region
         uint8_t *exch = nullptr;    // exchange records of the workgroups (parts > 1)
         uint8_t *mem = nullptr;     // the allocation that holds them all
@@ -603,7 +604,7 @@ int launch_blocks(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream
         A.err = ctx->flags + kFlagRange;
         A.tiles = ctx->act;
         A.nact = ctx->nact;
-        A.slots = ctx->chain.slots;
+        A.slot_of = ctx->by_region ? ctx->slot_of : nullptr;
         const bool samp = ctx->cfg.time_sample > 0 && has_c && b > b0 &&
                           b % ctx->cfg.time_sample == 0;
         tvs::KTimer kt;
@@ -633,7 +634,7 @@ bool run_chain(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream_t 
     a.toff = ctx->bt_off;
     a.nact = ctx->nact;
     a.base = v.base;
-    a.act = ctx->act;
+    a.act = c.act;
     a.reg = c.reg;
     a.wepl = ctx->hist + 12 * ctx->nh;
     a.n2 = ctx->norm2;
@@ -899,7 +900,7 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
 }
 
 // The chain's device data; without room for it the chain stays off.
-int chain_upload(tvs_ctx *ctx, const std::vector<int32_t> &reg, const std::vector<int32_t> &slots,
+int chain_upload(tvs_ctx *ctx, const std::vector<int32_t> &reg, const std::vector<int32_t> &tiles,
                  hipStream_t st)
 {
     auto &c = ctx->chain;
@@ -907,7 +908,7 @@ int chain_upload(tvs_ctx *ctx, const std::vector<int32_t> &reg, const std::vecto
     const size_t nbar = 4 * (size_t)(tvs::kChainShards + c.nreg) * 32;
     const size_t nexch = c.parts > 1 ? (size_t)c.nreg * c.parts * tvs::kChainExchBytes : 0;
     std::vector<int32_t> tab(reg);
-    tab.insert(tab.end(), slots.begin(), slots.end());
+    tab.insert(tab.end(), tiles.begin(), tiles.end());
     c.bytes = nbar + nexch + 4 * tab.size();
     if (ctx->bytes + c.bytes > ctx->budget || dalloc(ctx, &c.mem, c.bytes)) {
         ctx->err.clear();
@@ -917,7 +918,7 @@ int chain_upload(tvs_ctx *ctx, const std::vector<int32_t> &reg, const std::vecto
     c.bar = reinterpret_cast<uint32_t *>(c.mem);
     c.exch = c.mem + nbar;
     c.reg = reinterpret_cast<int32_t *>(c.mem + nbar + nexch);
-    c.slots = c.reg + reg.size();
+    c.act = c.reg + reg.size();
     HIPCHK(hipMemsetAsync(c.mem, 0, nbar + nexch, st));
     HIPCHK(hipMemcpyAsync(c.reg, tab.data(), 4 * tab.size(), hipMemcpyHostToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
@@ -930,11 +931,15 @@ int chain_upload(tvs_ctx *ctx, const std::vector<int32_t> &reg, const std::vecto
 // the DROP steps launch one workgroup per such tile only, in order of
 // decreasing entries over the scan, so that the longest lists are
 // dispatched first and do not trail the step.  Workgroup i of a step takes
-// slot i: tile act[i], whose lists are laid out in slot order (slot_of
-// inverts act; -1 for a tile no list crosses).  At least one tile is kept,
-// so that a step always has a workgroup to clear the next dot-product
-// buffer.
-int build_active_tiles(tvs_ctx *ctx, const uint32_t *btc, hipStream_t st)
+// tile busiest[i]; the lists are laid out in slot order, which is the same
+// or, where the chain runs, that of its regions (slot_of: tile -> slot, -1
+// for a tile no list crosses).  act is left in slot order, for the list
+// lengths; the caller then puts busiest there.  Both, like every argument of
+// the per-block launches, stay until the next load: a caller's graph may hold
+// them.  At least one tile is kept, so that a step always has a workgroup to
+// clear the next dot-product buffer.
+int build_active_tiles(tvs_ctx *ctx, const uint32_t *btc, std::vector<int32_t> &busiest,
+                       hipStream_t st)
 {
     const int64_t nt = ctx->ntiles;
     uint32_t *total = nullptr;
@@ -954,14 +959,12 @@ int build_active_tiles(tvs_ctx *ctx, const uint32_t *btc, hipStream_t st)
     std::stable_sort(a.begin(), a.end(), busier);
     if (a.empty()) a.push_back(0);
     ctx->nact = (int64_t)a.size();
-    std::vector<int32_t> reg, busiest, placed = a;
-    if (plan_chain(ctx, f, placed, reg)) {
+    busiest = a;
+    std::vector<int32_t> reg, placed = a;
+    ctx->by_region = plan_chain(ctx, f, placed, reg);
+    if (ctx->by_region) {
         a.swap(placed);
-        busiest.resize(a.size());
-        for (size_t i = 0; i < a.size(); i++) busiest[i] = (int32_t)i;
-        std::stable_sort(busiest.begin(), busiest.end(),
-                         [&](int32_t x, int32_t y) { return busier(a[(size_t)x], a[(size_t)y]); });
-        rc = chain_upload(ctx, reg, busiest, st);
+        rc = chain_upload(ctx, reg, a, st);
         if (rc) return rc;
     }
     std::vector<int32_t> inv((size_t)std::max<int64_t>(nt, 1), -1);
@@ -1087,10 +1090,10 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
         cleanup();
         return fail(ctx, TVS_EDEVICE, std::string("tile lists: ") + hipGetErrorString(e));
     }
-    // the dispatch slots, then the lists of every block laid out in slot
-    // order: a step's workgroup i finds its list bounds at [b * nact + i]
-    // without first looking up its tile
-    rc = build_active_tiles(ctx, btc, st);
+    // the slots, then the lists of every block laid out in slot order: their
+    // bounds are at [b * nact + slot]
+    std::vector<int32_t> busiest;
+    rc = build_active_tiles(ctx, btc, busiest, st);
     nsbc = ctx->nblocks * ctx->nact;
     if (!rc) rc = dalloc(ctx, &ctx->bt_off, (size_t)bt_len(ctx));
     if (!rc) rc = dalloc(ctx, &sbc, (size_t)std::max<int64_t>(nsbc, 1));
@@ -1099,6 +1102,10 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
         return rc;
     }
     e = tvs::launch_slot_counts(btc, ctx->act, ctx->nact, ctx->nblocks, ctx->ntiles, sbc, st);
+    // from here on in dispatch order
+    if (e == hipSuccess && ctx->by_region)
+        e = hipMemcpyAsync(ctx->act, busiest.data(), sizeof(int32_t) * busiest.size(),
+                           hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
         e = tvs::launch_scan(reinterpret_cast<const int32_t *>(sbc), nsbc, ctx->bt_off, tmp, st);
     if (e == hipSuccess)
@@ -2132,7 +2139,7 @@ int batch_cycle(tvs_ctx *ctx, int nmax, hipStream_t st)
         A.err = ctx->flags + kFlagRange;
         A.tiles = ctx->act;
         A.nact = ctx->nact;
-        A.slots = ctx->chain.slots;
+        A.slot_of = ctx->by_region ? ctx->slot_of : nullptr;
         HIPCHK(tvs::launch_drop_tiles_batch(A, Bt.b, ctx->ntiles, ctx->bthreads, ctx->bgroup, st));
         if (otf && first_of_chunk && c >= 1 && c - 1 + NB < nchunks) {
             // the launch above was the last to read chunk c - 1's buffer
@@ -2557,7 +2564,7 @@ int tvs_autotune_batch(tvs_ctx *ctx, const tvs_params *p, int32_t S, const char 
                     A.err = ctx->flags + kFlagRange;
                     A.tiles = ctx->act;
                     A.nact = ctx->nact;
-                    A.slots = ctx->chain.slots;
+                    A.slot_of = ctx->by_region ? ctx->slot_of : nullptr;
                     e = tvs::launch_drop_tiles_batch(A, Bt.b, ctx->ntiles, ctx->bthreads,
                                                      ctx->bgroup, st);
                 }

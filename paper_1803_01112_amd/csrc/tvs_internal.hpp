@@ -270,9 +270,9 @@ struct DropTileArgs {
     // nact workgroups
     const int32_t *tiles = nullptr;
     int64_t nact = 0;
-    // dispatch order of the slots (busiest first) where the slots themselves
-    // are laid out by region; null: slot order
-    const int32_t *slots = nullptr;
+    // slot of every tile's lists where the slots are laid out by region; null:
+    // workgroup i's lists are those of slot i
+    const int32_t *slot_of = nullptr;
 };
 
 // Start/stop events of the kernels of one block (first and second launch);
@@ -312,7 +312,7 @@ struct ChainArgs {
     uint32_t qshift = 31, rowmask = 0xffffffu;
     const int64_t *toff = nullptr;    // list starts by (block, slot)
     int64_t nact = 0, base = 0;
-    const int32_t *act = nullptr;     // slot -> tile
+    const int32_t *act = nullptr;     // slot -> tile, regions one after the other
     const int32_t *reg = nullptr;     // nreg + 1: first slot of each region
     const float *wepl = nullptr, *n2 = nullptr;   // per history
     long long *dot = nullptr;         // 3 x B fixed-point row dot products
