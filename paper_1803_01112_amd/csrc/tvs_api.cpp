@@ -233,18 +233,22 @@ struct tvs_ctx {
     double tot_ms[6] = {0, 0, 0, 0, 0, 0};
     int64_t tot_n[6] = {0, 0, 0, 0, 0, 0};
 
-    // the resident DROP chain (plan_chain); off when the grid or the block does not suit it
+    // the resident DROP chain (plan_chain) of the loaded histories
     struct Chain {
-        bool on = false;
+        bool planned = false;       // the grid and the blocks suit it
+        bool failed = false;        // a barrier timed out: its counters no longer match
         bool refused = false;       // a launch was refused (rows of several chunks on the fly)
         int nreg = 0, parts = 1, tmax = 0, ns = 0;
-        int32_t *reg = nullptr;     // nreg + 1: first slot of each region
-        int32_t *act = nullptr;     // nact: slot -> tile
+        std::vector<int32_t> tab;   // first slot of each region (nreg + 1), then slot -> tile
+        // device workspace, given back when a call needs its room (dalloc, chain_restore)
+        int32_t *reg = nullptr;     // tab's two parts
+        int32_t *act = nullptr;
         uint32_t *bar = nullptr;    // barrier counters: all workgroups', then one per region
         uint8_t *exch = nullptr;    // exchange records of the workgroups (parts > 1)
         uint8_t *mem = nullptr;     // the allocation that holds them all
         size_t bytes = 0;
         uint32_t epoch = 0, sub_epoch = 0;
+        bool on() const { return planned && mem && !failed; }
     } chain;
 
     // batched reconstructions
@@ -285,6 +289,8 @@ int fail(tvs_ctx *ctx, int code, const std::string &msg)
 
 void chain_release(tvs_ctx *ctx);
 
+size_t chain_bar_bytes(int nreg) { return 4 * (size_t)(tvs::kChainShards + nreg) * 32; }
+
 // Frees what tvs_load_histories has given back and not taken again.
 void drop_spare(tvs_ctx *ctx)
 {
@@ -308,8 +314,10 @@ int dalloc(tvs_ctx *ctx, T **p, size_t count)
         return TVS_OK;
     }
     if (ctx->bytes + ctx->spare_bytes + bytes > ctx->budget) drop_spare(ctx);
-    // the chain's small workspace gives way to whatever else needs the room
-    if (ctx->bytes + bytes > ctx->budget) chain_release(ctx);
+    // the chain's workspace gives way to what then fits (chain_restore)
+    if (ctx->bytes + bytes > ctx->budget && ctx->chain.mem &&
+        ctx->bytes - ctx->chain.bytes + bytes <= ctx->budget)
+        chain_release(ctx);
     if (ctx->bytes + bytes > ctx->budget)
         return fail(ctx, TVS_ENOMEM,
                     "footprint " + std::to_string(ctx->bytes + bytes) + " B exceeds budget " +
@@ -347,12 +355,53 @@ void dfree(tvs_ctx *ctx, T **p, size_t count)
     }
 }
 
+// Gives the chain's workspace back to the device (not to the next allocations
+// of a load: the room is wanted now).
 void chain_release(tvs_ctx *ctx)
 {
     auto &c = ctx->chain;
+    const bool recycle = ctx->recycle;
+    ctx->recycle = false;
     dfree(ctx, &c.mem, c.bytes);
-    c = tvs_ctx::Chain();
+    ctx->recycle = recycle;
+    c.reg = c.act = nullptr;
+    c.bar = nullptr;
+    c.exch = nullptr;
 }
+
+// Forms the chain's workspace again where it is missing and there is room:
+// counters and exchange records (cleared), then the tables.
+void chain_restore(tvs_ctx *ctx)
+{
+    auto &c = ctx->chain;
+    if (!c.planned || c.failed || c.mem || ctx->bytes + c.bytes > ctx->budget) return;
+    const std::string err = ctx->err;
+    const size_t nbar = chain_bar_bytes(c.nreg);
+    const size_t ntab = 4 * c.tab.size(), clear = c.bytes - ntab;
+    if (dalloc(ctx, &c.mem, c.bytes) == TVS_OK) {
+        c.bar = reinterpret_cast<uint32_t *>(c.mem);
+        c.exch = c.mem + nbar;
+        c.reg = reinterpret_cast<int32_t *>(c.mem + clear);
+        c.act = c.reg + c.nreg + 1;
+        c.epoch = c.sub_epoch = 0;
+        hipError_t e = hipMemsetAsync(c.mem, 0, clear, ctx->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(c.reg, c.tab.data(), ntab, hipMemcpyHostToDevice, ctx->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            chain_release(ctx);
+        }
+    }
+    ctx->err = err;
+}
+
+// At the end of every call that allocates: what the call took from the chain
+// and has given back is the chain's again.
+struct ChainBack {
+    tvs_ctx *c;
+    ~ChainBack() { chain_restore(c); }
+};
 
 int64_t bt_len(const tvs_ctx *ctx) { return ctx->nblocks * ctx->nact + 1; }
 
@@ -372,7 +421,8 @@ void free_histories(tvs_ctx *ctx)
     ctx->mlp.nj = 0;
     dfree(ctx, &ctx->segtab, (size_t)ctx->nseg);
     dfree(ctx, &ctx->bt_off, (size_t)bt_len(ctx));
-    chain_release(ctx);
+    dfree(ctx, &ctx->chain.mem, ctx->chain.bytes);
+    ctx->chain = tvs_ctx::Chain();
     dfree(ctx, &ctx->act, (size_t)std::max<int64_t>(ctx->nact, 1));
     dfree(ctx, &ctx->slot_of, (size_t)std::max<int64_t>(ctx->ntiles, 1));
     ctx->nact = 0;
@@ -524,7 +574,7 @@ int check_flags(tvs_ctx *ctx, hipStream_t st)
         return fail(ctx, TVS_EDEVICE, "a row walk disagreed with its load-time tile lists");
     if (f[kFlagRange] & 4u) {
         // the barrier's counters no longer match: launch block by block from here on
-        ctx->chain.on = false;
+        ctx->chain.failed = true;
         return fail(ctx, TVS_EDEVICE, "a workgroup of the DROP chain did not reach its barrier");
     }
     if (f[kFlagRange])
@@ -694,7 +744,7 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
     // rows of several chunks are formed beside per-block launches again
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     const bool several = otf && ctx->nbuf > 1;
-    const bool chain = ctx->chain.on && !(several && ctx->chain.refused) &&
+    const bool chain = ctx->chain.on() && !(several && ctx->chain.refused) &&
                        hipStreamIsCapturing(st, &cap) == hipSuccess &&
                        cap == hipStreamCaptureStatusNone;
     // for the chain: the buffers as one, filled (the first time beside the TV
@@ -807,14 +857,14 @@ int count_rows(tvs_ctx *ctx, int64_t first, int64_t n, int64_t *row_off_dev, hip
 }
 
 // Places the active tiles in regions of the resident chain (chain.hip), one
-// region per workgroup: reorders a (the tiles by slot) and fills reg, the
-// first slot of each region.  False where the chain does not fit: explicit
+// region per workgroup: reorders a (the tiles by slot) and describes them in
+// the context's chain.  False where the chain does not fit: explicit
 // launch shapes, blocks of more rows than a packed entry names, images whose
 // crossed tiles do not fit the device's LDS.
-bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<int32_t> &a,
-                std::vector<int32_t> &reg)
+bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<int32_t> &a)
 {
     auto &c = ctx->chain;
+    std::vector<int32_t> reg;
     const int64_t B = ctx->cfg.block_size;
     if (ctx->cfg.sweep_kernel != 0 || ctx->cfg.tile_threads != 0 || B > tvs::kChainMaxB) return false;
     int cus = 0, coop = 0;
@@ -896,34 +946,12 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
     c.nreg = (int)reg.size() - 1;
     c.tmax = 0;
     for (int r = 0; r < c.nreg; r++) c.tmax = std::max(c.tmax, reg[(size_t)r + 1] - reg[(size_t)r]);
-    return true;
-}
-
-// The chain's device data; without room for it the chain stays off.
-int chain_upload(tvs_ctx *ctx, const std::vector<int32_t> &reg, const std::vector<int32_t> &tiles,
-                 hipStream_t st)
-{
-    auto &c = ctx->chain;
-    // one allocation: counters and exchange records (cleared), then the tables
-    const size_t nbar = 4 * (size_t)(tvs::kChainShards + c.nreg) * 32;
+    c.tab = reg;
+    c.tab.insert(c.tab.end(), a.begin(), a.end());
     const size_t nexch = c.parts > 1 ? (size_t)c.nreg * c.parts * tvs::kChainExchBytes : 0;
-    std::vector<int32_t> tab(reg);
-    tab.insert(tab.end(), tiles.begin(), tiles.end());
-    c.bytes = nbar + nexch + 4 * tab.size();
-    if (ctx->bytes + c.bytes > ctx->budget || dalloc(ctx, &c.mem, c.bytes)) {
-        ctx->err.clear();
-        chain_release(ctx);
-        return TVS_OK;
-    }
-    c.bar = reinterpret_cast<uint32_t *>(c.mem);
-    c.exch = c.mem + nbar;
-    c.reg = reinterpret_cast<int32_t *>(c.mem + nbar + nexch);
-    c.act = c.reg + reg.size();
-    HIPCHK(hipMemsetAsync(c.mem, 0, nbar + nexch, st));
-    HIPCHK(hipMemcpyAsync(c.reg, tab.data(), 4 * tab.size(), hipMemcpyHostToDevice, st));
-    HIPCHK(hipStreamSynchronize(st));
-    c.on = true;
-    return TVS_OK;
+    c.bytes = chain_bar_bytes(c.nreg) + nexch + 4 * c.tab.size();
+    c.planned = true;
+    return true;
 }
 
 // The tiles that some block's lists cross (a tile outside the scanned
@@ -960,13 +988,9 @@ int build_active_tiles(tvs_ctx *ctx, const uint32_t *btc, std::vector<int32_t> &
     if (a.empty()) a.push_back(0);
     ctx->nact = (int64_t)a.size();
     busiest = a;
-    std::vector<int32_t> reg, placed = a;
-    ctx->by_region = plan_chain(ctx, f, placed, reg);
-    if (ctx->by_region) {
-        a.swap(placed);
-        rc = chain_upload(ctx, reg, a, st);
-        if (rc) return rc;
-    }
+    std::vector<int32_t> placed = a;
+    ctx->by_region = plan_chain(ctx, f, placed);
+    if (ctx->by_region) a.swap(placed);
     std::vector<int32_t> inv((size_t)std::max<int64_t>(nt, 1), -1);
     for (size_t i = 0; i < a.size(); i++) inv[(size_t)a[i]] = (int32_t)i;
     rc = dalloc(ctx, &ctx->act, a.size());
@@ -1460,6 +1484,7 @@ int tvs_load_histories(tvs_ctx *ctx, int64_t n, const tvs_histories *h, int on_d
         }
     } recycle{ctx};
     ctx->recycle = true;
+    ChainBack back{ctx};
     free_histories(ctx);
     reset_state(ctx);
     HIPCHK(hipMemsetAsync(ctx->x, 0, sizeof(double) * ctx->nvox, st));
@@ -1617,6 +1642,7 @@ int tvs_initial_fbp(tvs_ctx *ctx, const tvs_fbp_params *p, float *out, int on_de
     // table, the image.  nt is even.
     const size_t words = (size_t)nb / 2 * 5 + (size_t)nb + (size_t)(2 * A) + (size_t)ctx->nimg;
     double *work = nullptr;
+    ChainBack back{ctx};
     rc = dalloc(ctx, &work, words);
     if (rc) return rc;
     auto *slots = reinterpret_cast<unsigned long long *>(work);
@@ -1740,6 +1766,7 @@ int tvs_hull_detect(tvs_ctx *ctx, const tvs_hull_params *p, uint8_t *hull, int o
     uint8_t *hd = nullptr;
     // the mask's buffer holds the full-voxel bits until the mask is written
     const size_t nhd = std::max((size_t)ctx->nimg, (size_t)(4 * tvs::hull_full_words(ctx->gd)));
+    ChainBack back{ctx};
     int rc = dalloc(ctx, &cnt, (size_t)(2 * ctx->nimg));
     if (!rc) rc = dalloc(ctx, &hd, nhd);
     if (rc) {
@@ -1967,6 +1994,7 @@ int tvs_debug_rows(tvs_ctx *ctx, int64_t first, int64_t count, int64_t *row_nnz,
     HIPCHK(hipSetDevice(ctx->cfg.device));
     hipStream_t st = ctx->stream;
     int64_t *off = nullptr;
+    ChainBack back{ctx};
     int rc = dalloc(ctx, &off, (size_t)(count + 1));
     if (rc) return rc;
     rc = count_rows(ctx, first, count, off, st);
@@ -2179,6 +2207,7 @@ int tvs_iterate_batch(tvs_ctx *ctx, const tvs_params *p, int32_t S, int32_t K, v
     HIPCHK(hipStreamSynchronize(ctx->stream));
     if (ctx->cfg.path_mode == TVS_PATH_ON_THE_FLY)
         for (int q = 0; q < kChunkBuffers; q++) HIPCHK(hipStreamWaitEvent(st, ctx->ev_free[q], 0));
+    ChainBack back{ctx};
     auto &B = ctx->batch;
     bool same = B.valid && B.S == S;
     for (int q = 0; same && q < S; q++) same = same_params(B.p[q], p[q]);
@@ -2364,6 +2393,7 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
         return TVS_OK;
     }
     HIPCHK(hipStreamSynchronize(ctx->fill_stream));
+    ChainBack back{ctx};
     double *saved = nullptr;
     int rc = dalloc(ctx, &saved, (size_t)ctx->nvox);
     if (rc) return rc;
@@ -2374,10 +2404,10 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
     // beside them (batches use both too); the chain goes on where it fits
     struct ChainOff {
         tvs_ctx *c;
-        bool on;
-        ~ChainOff() { c->chain.on = on && c->chain.reg; }
-    } chain_off{ctx, ctx->chain.on};
-    ctx->chain.on = false;
+        bool planned;
+        ~ChainOff() { c->chain.planned = planned; }
+    } chain_off{ctx, ctx->chain.planned};
+    ctx->chain.planned = false;
     double best = 1e300;
     int nc = 0;
     for (int sw = 1; sw <= 2 && rc == TVS_OK; sw++) {
@@ -2528,6 +2558,7 @@ int tvs_autotune_batch(tvs_ctx *ctx, const tvs_params *p, int32_t S, const char 
     }
     HIPCHK(hipStreamSynchronize(ctx->fill_stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
+    ChainBack back{ctx};
     int rc = batch_init(ctx, p, S, st);
     if (rc) return rc;
     auto &Bt = ctx->batch;
