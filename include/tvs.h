@@ -336,6 +336,14 @@ int tvs_get_stats(tvs_ctx *ctx, tvs_stats *out);
  * of records held.  The log is cleared by tvs_set_image / tvs_load_histories. */
 int tvs_get_step_log(tvs_ctx *ctx, tvs_step_log *out, int64_t cap, int64_t *n);
 
+/* How the next sweep would run, for inspection: out[0] is 1 for the resident
+ * chain (many DROP blocks per launch), 0 for launches per block, out[1] the
+ * threads per tile workgroup of the latter.  what: 0 reads only; 1 first waits
+ * for the context's stream and puts the chain into the state that a workgroup
+ * missing at its barrier leaves (for tests of that error).  TVS_EINVAL for
+ * another what; TVS_ESTATE before tvs_load_histories. */
+int tvs_debug_sweep(tvs_ctx *ctx, int32_t what, int32_t out[2]);
+
 /* Exports the rows of histories [first, first+count) for inspection: row
  * lengths (row_nnz[count]), voxel indices and chords concatenated in history
  * order (at most cap entries), and ||a||^2 (norm2[count]); all host arrays.

@@ -112,7 +112,8 @@ struct Lds {
     int *bnd;            // ring: the list's starts by tile of the region
     int *cut;            // ring: first and last entry of this workgroup's share of the list
     uint32_t *misc;      // [0] wait result, [1] a large correction was met, [2] one of its own,
-                         // of even and odd blocks: [4], [5] rows in the table, [6], [7] words in hit
+                         // [3] the counters are not to be used, of even and odd blocks:
+                         // [4], [5] rows in the table, [6], [7] words in hit
     uint16_t *used;      // slots taken in the tables of even and odd blocks
     uint16_t *hit;       // words with hits (one workgroup per region)
 };
@@ -562,7 +563,10 @@ struct Chain {
         }
         __syncthreads();
         const bool ok = L.misc[0] != 0u;
-        if (!ok && t == 0) atomicOr(A.err, 4u);
+        if (!ok && t == 0) {
+            atomicOr(A.err, 4u);
+            store_agent(A.dead, 1u);
+        }
         return ok;
     }
 
@@ -582,7 +586,10 @@ struct Chain {
             L.tv[s] = 0;
             L.tag[s] = L.tag[A.ns + s] = kNone;
         }
-        if (t < 8) L.misc[t] = 0u;
+        if (t < 8 && t != 3) L.misc[t] = 0u;
+        // after a time-out the counters no longer match the launches queued
+        // behind it: those leave at once, whatever became of the error flag
+        if (t == 3) L.misc[3] = load_agent(A.dead);
         if (t < 256) L.inv[t] = 1.0 / (double)t;
         // dot products of blocks b - 1, b and b + 1 (three buffers in turn)
         long long *d0 = A.dot + ((A.b0 + 2) % 3) * A.B, *d1 = A.dot + (A.b0 % 3) * A.B,
@@ -591,6 +598,10 @@ struct Chain {
         int64_t off = request_bounds(A.b0 + 3);
         clear_dots(d1);
         __syncthreads();
+        if (L.misc[3]) {
+            if (t == 0) atomicOr(A.err, 4u);
+            return;
+        }
         Raw<E> raw;
         Ents<E> C, P;
         request<false>(span(A.b0), 0, raw);

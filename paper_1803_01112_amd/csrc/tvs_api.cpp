@@ -243,7 +243,8 @@ struct tvs_ctx {
         // device workspace, given back when a call needs its room (dalloc, chain_restore)
         int32_t *reg = nullptr;     // tab's two parts
         int32_t *act = nullptr;
-        uint32_t *bar = nullptr;    // barrier counters: all workgroups', then one per region
+        uint32_t *bar = nullptr;    // barrier counters: all workgroups', then one per region;
+                                    // behind them the mark of a wait that timed out
         uint8_t *exch = nullptr;    // exchange records of the workgroups (parts > 1)
         uint8_t *mem = nullptr;     // the allocation that holds them all
         size_t bytes = 0;
@@ -289,7 +290,7 @@ int fail(tvs_ctx *ctx, int code, const std::string &msg)
 
 void chain_release(tvs_ctx *ctx);
 
-size_t chain_bar_bytes(int nreg) { return 4 * (size_t)(tvs::kChainShards + nreg) * 32; }
+size_t chain_bar_bytes(int nreg) { return 4 * (size_t)(tvs::kChainShards + nreg + 1) * 32; }
 
 // Frees what tvs_load_histories has given back and not taken again.
 void drop_spare(tvs_ctx *ctx)
@@ -394,6 +395,12 @@ void chain_restore(tvs_ctx *ctx)
         }
     }
     ctx->err = err;
+}
+
+// Word of the workspace that a timed-out wait sets, behind the counters.
+uint32_t *chain_dead(tvs_ctx *ctx)
+{
+    return ctx->chain.bar + (tvs::kChainShards + ctx->chain.nreg) * 32;
 }
 
 // At the end of every call that allocates: what the call took from the chain
@@ -573,7 +580,7 @@ int check_flags(tvs_ctx *ctx, hipStream_t st)
     if (f[kFlagLists] || (f[kFlagRange] & 2u))
         return fail(ctx, TVS_EDEVICE, "a row walk disagreed with its load-time tile lists");
     if (f[kFlagRange] & 4u) {
-        // the barrier's counters no longer match: launch block by block from here on
+        // the barrier's counters no longer match: launch block by block until the next load
         ctx->chain.failed = true;
         return fail(ctx, TVS_EDEVICE, "a workgroup of the DROP chain did not reach its barrier");
     }
@@ -699,6 +706,7 @@ bool run_chain(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream_t 
     a.err = ctx->flags + kFlagRange;
     a.bar = c.bar;
     a.sub = c.bar + tvs::kChainShards * 32;
+    a.dead = chain_dead(ctx);
     a.exch = c.exch;
     a.nreg = c.nreg;
     a.parts = c.parts;
@@ -1978,6 +1986,24 @@ int tvs_get_step_log(tvs_ctx *ctx, tvs_step_log *out, int64_t cap, int64_t *n)
     *n = (int64_t)ctx->log.size();
     int64_t m = std::min<int64_t>(cap, *n);
     if (m > 0) std::memcpy(out, ctx->log.data(), sizeof(tvs_step_log) * (size_t)m);
+    return TVS_OK;
+}
+
+int tvs_debug_sweep(tvs_ctx *ctx, int32_t what, int32_t out[2])
+{
+    if (!ctx || !out) return TVS_EINVAL;
+    ctx->err.clear();
+    if (what < 0 || what > 1) return fail(ctx, TVS_EINVAL, "what must lie in 0..1");
+    if (!ctx->loaded) return fail(ctx, TVS_ESTATE, "no histories loaded");
+    HIPCHK(hipSetDevice(ctx->cfg.device));
+    auto &c = ctx->chain;
+    if (what == 1 && c.on()) {
+        const uint32_t one = 1;
+        HIPCHK(hipStreamSynchronize(ctx->stream));
+        HIPCHK(hipMemcpy(chain_dead(ctx), &one, sizeof(one), hipMemcpyHostToDevice));
+    }
+    out[0] = c.on();
+    out[1] = ctx->threads;
     return TVS_OK;
 }
 

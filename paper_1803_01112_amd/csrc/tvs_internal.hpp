@@ -325,6 +325,7 @@ struct ChainArgs {
     uint32_t *err = nullptr;          // bits 0 and 1 as in DropTileArgs, bit 2: a wait timed out
     uint32_t *bar = nullptr;          // barrier counters (kChainShards x 32 words), only counted up
     uint32_t *sub = nullptr;          // nreg x 32 words: a region's own barrier (parts > 1)
+    uint32_t *dead = nullptr;         // set by a wait that timed out: bar and sub are not to be used
     uint32_t epoch = 0, sub_epoch = 0;   // barriers passed before this launch
     void *exch = nullptr;             // nreg * parts exchange records (parts > 1)
     int32_t nreg = 0, parts = 1, tmax = 0;

@@ -28,7 +28,7 @@ EXPORTED = ("tvs_config_default", "tvs_create", "tvs_destroy", "tvs_load_histori
             "tvs_server_footprint", "tvs_server_submit", "tvs_server_query", "tvs_server_wait",
             "tvs_server_get_counters", "tvs_server_destroy", "tvs_autotune", "tvs_initial_fbp",
             "tvs_initial_fbp_noalloc", "tvs_hull_detect",
-            "tvs_autotune_batch")
+            "tvs_autotune_batch", "tvs_debug_sweep")
 
 
 class TvsError(RuntimeError):
@@ -175,6 +175,8 @@ def load_library(path: str = LIB):
     L.tvs_hull_detect.restype = C.c_int
     L.tvs_debug_rows.argtypes = [C.c_void_p, C.c_int64, C.c_int64, P(C.c_int64), P(C.c_int32),
                                  _FP, _FP, C.c_int64]
+    L.tvs_debug_sweep.argtypes = [C.c_void_p, C.c_int32, P(C.c_int32)]
+    L.tvs_debug_sweep.restype = C.c_int
     L.tvs_strerror.argtypes = [C.c_int]
     L.tvs_strerror.restype = C.c_char_p
     L.tvs_last_error.argtypes = [C.c_void_p]
@@ -391,6 +393,13 @@ class Context:
                             int(bool(st.get("tv_check", False))), v, float(st.get("tv_eps", 0.0)),
                             int(st.get("seed", 0)) & (2**64 - 1), float(st.get("gamma", 0.5)))
         return S, arr
+
+    def debug_sweep(self, what=0):
+        """(chain, threads): whether the next sweep takes the resident chain, and
+        the threads per tile of its per-block launches (what: see the header)."""
+        out = (C.c_int32 * 2)()
+        self._check(self._L.tvs_debug_sweep(self._h, int(what), out), "tvs_debug_sweep")
+        return bool(out[0]), int(out[1])
 
     def iterate_batch(self, K, settings, stream=None):
         """K cycles of S settings together; settings: list of dicts with keys
