@@ -340,8 +340,8 @@ int tvs_get_step_log(tvs_ctx *ctx, tvs_step_log *out, int64_t cap, int64_t *n);
  * chain (many DROP blocks per launch), 0 for launches per block, out[1] the
  * threads per tile workgroup of the latter.  what: 0 reads only; 1 first waits
  * for the context's stream and puts the chain into the state that a workgroup
- * missing at its barrier leaves (for tests of that error).  TVS_EINVAL for
- * another what; TVS_ESTATE before tvs_load_histories. */
+ * missing at its barrier leaves, 2 lets the chain's next launch count as
+ * refused (for tests of these errors).  TVS_EINVAL for another what; TVS_ESTATE before tvs_load_histories. */
 int tvs_debug_sweep(tvs_ctx *ctx, int32_t what, int32_t out[2]);
 
 /* Exports the rows of histories [first, first+count) for inspection: row

@@ -49,6 +49,13 @@ constexpr int32_t kLongBlock = 8192;
 // Blocks one launch of the resident chain takes at most (about 6 ms; a
 // launch's own cost is some 20 us).
 constexpr int64_t kChainBlocks = 1024;
+// Sweeps on the fly that go by launches beside the row formation after a chain
+// launch was refused (another process held the cooperative queue) before the
+// chain is tried again.  A sweep that finds it still refused has formed its rows
+// first and launches the blocks then (3 M rows of 200x200x16 19.3 ms against
+// 18.05 beside each other and 14.8 with the chain; of 256x256x32 22.2, 21.7
+// and 17.8), so one in sixteen costs 0.2 to 0.5 %.
+constexpr int kRefusedSweeps = 15;
 constexpr int kChainTable = 2048;            // slots of its row table
 constexpr int kChainLds = 160 * 1024 - 256;  // LDS of a CU it may take
 
@@ -237,7 +244,9 @@ struct tvs_ctx {
     struct Chain {
         bool planned = false;       // the grid and the blocks suit it
         bool failed = false;        // a barrier timed out: its counters no longer match
-        bool refused = false;       // a launch was refused (rows of several chunks on the fly)
+        int refused = 0;            // sweeps until it is tried again after a refused launch
+                                    // (rows of several chunks on the fly)
+        bool refuse = false;        // tvs_debug_sweep: the next launch counts as refused
         int nreg = 0, parts = 1, tmax = 0, ns = 0;
         std::vector<int32_t> tab;   // first slot of each region (nreg + 1), then slot -> tile
         // device workspace, given back when a call needs its room (dalloc, chain_restore)
@@ -678,6 +687,10 @@ int launch_blocks(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream
 bool run_chain(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream_t st)
 {
     auto &c = ctx->chain;
+    if (c.refuse) {
+        c.refuse = false;
+        return false;
+    }
     const int64_t B = ctx->cfg.block_size;
     const TileBlock v = block_view(ctx, b0, ctx->dot, B);
     tvs::ChainArgs a;
@@ -748,13 +761,17 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
     if (nh_run <= 0) return TVS_OK;
     const int64_t nb = (nh_run + B - 1) / B;
     const bool otf = ctx->cfg.path_mode == TVS_PATH_ON_THE_FLY;
-    // a cooperative launch is not captured; where it was refused before, the
-    // rows of several chunks are formed beside per-block launches again
+    // a cooperative launch is not captured
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     const bool several = otf && ctx->nbuf > 1;
-    const bool chain = ctx->chain.on() && !(several && ctx->chain.refused) &&
-                       hipStreamIsCapturing(st, &cap) == hipSuccess &&
-                       cap == hipStreamCaptureStatusNone;
+    bool chain = ctx->chain.on() && hipStreamIsCapturing(st, &cap) == hipSuccess &&
+                 cap == hipStreamCaptureStatusNone;
+    // after a refused launch the rows of several chunks are formed beside
+    // per-block launches again, for some sweeps
+    if (chain && several && ctx->chain.refused > 0) {
+        ctx->chain.refused--;
+        chain = false;
+    }
     // for the chain: the buffers as one, filled (the first time beside the TV
     // steps) and emptied in turn
     const int64_t NB = chain ? 1 : ctx->nbuf;
@@ -802,7 +819,7 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
         for (int64_t b = c0; b < c1;) {
             const int64_t e = chain ? std::min(c1, b + kChainBlocks) : c1;
             if (!chain || !run_chain(ctx, lambda, b, e, st)) {
-                if (chain) ctx->chain.refused = true;
+                if (chain) ctx->chain.refused = kRefusedSweeps;
                 int rc = launch_blocks(ctx, lambda, b, e, st);
                 if (rc) return rc;
             }
@@ -1993,7 +2010,7 @@ int tvs_debug_sweep(tvs_ctx *ctx, int32_t what, int32_t out[2])
 {
     if (!ctx || !out) return TVS_EINVAL;
     ctx->err.clear();
-    if (what < 0 || what > 1) return fail(ctx, TVS_EINVAL, "what must lie in 0..1");
+    if (what < 0 || what > 2) return fail(ctx, TVS_EINVAL, "what must lie in 0..2");
     if (!ctx->loaded) return fail(ctx, TVS_ESTATE, "no histories loaded");
     HIPCHK(hipSetDevice(ctx->cfg.device));
     auto &c = ctx->chain;
@@ -2002,7 +2019,8 @@ int tvs_debug_sweep(tvs_ctx *ctx, int32_t what, int32_t out[2])
         HIPCHK(hipStreamSynchronize(ctx->stream));
         HIPCHK(hipMemcpy(chain_dead(ctx), &one, sizeof(one), hipMemcpyHostToDevice));
     }
-    out[0] = c.on();
+    if (what == 2) c.refuse = true;
+    out[0] = c.on() && !(c.refused > 0 && ctx->nbuf > 1);
     out[1] = ctx->threads;
     return TVS_OK;
 }
