@@ -166,7 +166,7 @@ typedef struct {
     double tv_ms_total;    /* all perturbation steps of the call */
     double sweep_ms_total; /* all sweeps of the call */
     double rows_ms_total;  /* all row-formation launches of the call */
-    double drop_ms_total;  /* all DROP launches of the call */
+    double drop_ms_total;  /* all DROP launches of the call, without waits for rows */
     int64_t cycles_timed;  /* cycles of the call */
     int64_t rows_launches; /* row-formation launches of the call */
     int64_t drop_launches; /* DROP chains timed (one per sweep) */

@@ -810,10 +810,10 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
             if (rc) return rc;
         }
     }
-    long e0 = mark(ctx, st);
     for (int64_t c = 0; c < nchunks; c++) {
         const int64_t c0 = c * step / B, c1 = std::min(nb, ((c + 1) * step + B - 1) / B);
         if (otf) HIPCHK(hipStreamWaitEvent(st, ctx->ev_filled[chunk_buffer(ctx, c)], 0));
+        const long e0 = mark(ctx, st);      // past the wait for the rows
         // at most kChainBlocks blocks a launch, so that reconstructions on
         // other streams, whose chains wait for this one, get their turn
         for (int64_t b = c0; b < c1;) {
@@ -825,6 +825,7 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
             }
             b = e;
         }
+        span(ctx, 3, e0, mark(ctx, st), c == 0 ? 1 : 0);
         if (otf) {
             if (chain) {
                 for (int q = 0; q < ctx->nbuf; q++) HIPCHK(hipEventRecord(ctx->ev_free[q], st));
@@ -837,7 +838,6 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
             }
         }
     }
-    span(ctx, 3, e0, mark(ctx, st));
     // the ring continues with the next sweep, whose first chunks take the
     // buffers freed first
     if (otf && !chain) ctx->cbase = (ctx->cbase + nchunks) % NB;
