@@ -96,9 +96,10 @@ typedef struct {
                                 2: the same work in two launches per block.
                                 The images are the same */
     int32_t tile_threads;    /* threads per image-tile workgroup of the per-block launches
-                                (64, 128, 256; sweep_kernel 0 is then read as 1); 0: 128 on the fly and for blocks of
-                                fewer than 8,192 histories on grids of more than 16 image
-                                tiles per CU, else 256 */
+                                (64, 128, 256; sweep_kernel 0 is then read as 1); 0: the
+                                library's choice at every load: 128 on the fly with
+                                several chunks and where many tiles have short lists,
+                                else 256 */
     int32_t time_sample;     /* k > 0: kernel-stamped HIP events on the launches of every
                                 k-th DROP block, or events around every launch of many
                                 blocks (durations per block in tvs_stats); 0: off */

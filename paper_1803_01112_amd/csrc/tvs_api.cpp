@@ -40,11 +40,6 @@ constexpr int64_t kDevLogCap = 4096;
 // formation stream can form the next sweep's first chunk while the DROP
 // chain still reads the last two of this sweep.
 constexpr int kChunkBuffers = 3;
-// Blocks from which a tile's lists keep 256 lanes busy for several rounds, so that
-// fewer rounds of workgroups no longer pay (two cycles of 4 M rows of 256x256x32 in a
-// 6-byte store with 128 / 256 lanes: 21.26 / 21.31 ms at B = 6,400, 17.00 / 16.25 at
-// 12,800, 13.88 / 13.20 at 25,600, 12.25 / 11.50 at 51,200)
-constexpr int32_t kLongBlock = 8192;
 
 // Blocks one launch of the resident chain takes at most (about 6 ms; a
 // launch's own cost is some 20 us).
@@ -205,6 +200,7 @@ struct tvs_ctx {
     std::vector<int64_t> chunk_base;  // entry offset of each chunk start (and the end)
     double big = 0.0, dot_max = 0.0;  // fixed-point ranges of the DROP kernels
     int threads = 256;              // threads per tile workgroup
+    bool tuned = false;             // by tvs_autotune (else tile_lanes at every load)
     int split = 0;                  // 1: two launches per block
     int bthreads = 256;             // batched DROP step: threads per workgroup
     int bgroup = 4;                 // batched DROP step: settings per pass through LDS
@@ -1030,6 +1026,28 @@ int build_active_tiles(tvs_ctx *ctx, const uint32_t *btc, std::vector<int32_t> &
     return TVS_OK;
 }
 
+// Threads per tile workgroup of the launches per block for the loaded lists.
+// 128 on the fly with several chunks (they leave the row formation beside them
+// more room).  Else 256 on grids of up to 16 tiles per CU, twice the
+// workgroups of 256 that the device holds at once; on larger ones two more
+// rounds of workgroups pay only where the lists are long: from 18 entries per
+// crossed tile of a CU on.  Measured, us a block with 128 / 256 lanes (float32
+// store, 6-byte store alike), crossed tiles per CU and entries of a list:
+//   16.7: 151 11.4 / 12.6, 450 21.2 / 21.3, 590 25.9 / 25.4, 1209 43.5 / 41.0
+//   26:   240 21.4 / 21.9, 472 32.8 / 30.8, 967 56.0 / 49.8
+//   52:   236 35.5 / 39.9, 483 53.4 / 57.2, 967 92.8 / 92.6
+//   66:   295 49.0 / 52.6, 604 79.8 / 82.0, 1207 148 / 142
+//   208:  94 78.6 / 102, 387 168 / 190
+int tile_lanes(const tvs_ctx *ctx)
+{
+    const bool otf = ctx->cfg.path_mode == TVS_PATH_ON_THE_FLY;
+    if (otf && ctx->chunk_base.size() > 2) return 128;
+    if (ctx->ntiles <= 16 * (int64_t)ctx->cus) return 256;
+    const double nact = (double)ctx->nact;
+    const double list = (double)ctx->nnz / ((double)std::max<int64_t>(ctx->nblocks, 1) * nact);
+    return list >= 18.0 * nact / (double)ctx->cus ? 256 : 128;
+}
+
 // Lays out the tile lists of every block: row and segment counts, each
 // segment's place in its (block, tile) list, the list starts.  Sets nnz,
 // max_row, skipped, nseg, nblocks and the chunking.
@@ -1143,6 +1161,7 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
     // bounds are at [b * nact + slot]
     std::vector<int32_t> busiest;
     rc = build_active_tiles(ctx, btc, busiest, st);
+    if (!ctx->cfg.tile_threads && !ctx->tuned) ctx->threads = tile_lanes(ctx);
     nsbc = ctx->nblocks * ctx->nact;
     if (!rc) rc = dalloc(ctx, &ctx->bt_off, (size_t)bt_len(ctx));
     if (!rc) rc = dalloc(ctx, &sbc, (size_t)std::max<int64_t>(nsbc, 1));
@@ -1399,15 +1418,8 @@ int tvs_create(const tvs_grid *grid, const tvs_config *cfg_in, tvs_ctx **out)
         // (within a few % of the best share at 200x200x16 and 256x256x32;
         // tvs_autotune times the shares on the loaded histories)
         ctx->fill_wide_pct = cfg.fill_wide_pct < 0 ? 40 : std::min(cfg.fill_wide_pct, 100);
-        // Tile workgroup size: 128 lanes on the fly (they leave the row
-        // formation beside them more room) and for short blocks on grids of more
-        // tiles than twice the 256-lane workgroups the device holds at once
-        // (8 per CU: fewer rounds of workgroups per step); else 256 lanes,
-        // with which a step of a path store is shortest
-        const int64_t resident256 = 8 * (int64_t)(cus > 0 ? cus : 256);
-        const bool small = cfg.path_mode == TVS_PATH_ON_THE_FLY ||
-                           (ctx->ntiles > 2 * resident256 && cfg.block_size < kLongBlock);
-        ctx->threads = cfg.tile_threads ? cfg.tile_threads : (small ? 128 : 256);
+        // (0: tile_lanes at every load)
+        ctx->threads = cfg.tile_threads ? cfg.tile_threads : 256;
     }
 
     size_t freeb = 0, totalb = 0;
@@ -2422,6 +2434,7 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
             ctx->threads = out->tile_threads;
             ctx->split = out->sweep_kernel == 2 ? 1 : 0;
             ctx->fill_wide_pct = out->fill_wide_pct;
+            ctx->tuned = true;
             return TVS_OK;
         }
     }
@@ -2506,6 +2519,7 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
     }
     ctx->threads = out->tile_threads;
     ctx->split = out->sweep_kernel == 2 ? 1 : 0;
+    ctx->tuned = true;
     // on the fly: whole sweeps (the row formation beside the launches) for the
     // share of chunks formed at the row kernel's full occupancy; with one
     // chunk the share does not matter
