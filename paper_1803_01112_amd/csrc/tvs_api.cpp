@@ -786,6 +786,9 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
     auto fill = [&](int64_t c) -> int {
         const int64_t n = std::min(step, ctx->nh - c * step);
         tvs::TileFill f = chunk_fill(ctx, c * ctx->joined, n);
+        // nothing but the TV steps beside a single chunk: full occupancy (900 k rows
+        // of 200x200x16 with launches at B = 25,600: 4.0 ms a cycle, 4.65 held)
+        if (!several) f.room = 0;
         if (chain) {
             f.cap *= ctx->joined;
             f.max_wgs = 0;
@@ -902,13 +905,25 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
     // 200x200x16 takes 19.6 ms against 23.0, 60 M of 256x256x32 349 against 372,
     // 2 M of 200x200x16 in chunks of 64 k 12.8 against 18.0, of 6,400 57 against 146.
     const int n = (int)a.size();
-    // Many tiles and long lists: a launch's workgroups fill the device, and
-    // the chain's one workgroup per CU is bound by instruction issue (256x256x32
-    // at B = 25,600, 20,000 entries a CU: 44 us a block against 40 launched).
-    // Shorter lists or fewer tiles are the chain's (2,000 entries a CU: 7.2
-    // against 8.8 us).
-    const double avg = (double)ctx->nnz / (double)std::max<int64_t>(ctx->nblocks, 1);
-    if (n >= 4 * cus && avg > 8192.0 * cus) return false;
+    // Long lists: the chain's one workgroup per CU is bound by instruction issue,
+    // its time a block that of a CU's entries.  A launch's time goes with the
+    // longest list instead: up to 8 tiles per CU are in work at once, so the more
+    // of them share the entries, the shorter it is; past 8 it takes several
+    // rounds.  So the chain wins up to 40,000 entries per CU divided by the tiles
+    // per CU, or 1,000 times them; with few tiles always.  Measured, entries per
+    // CU and us a block of chain / launches (float32 store; the 6-byte store and
+    // rows on the fly within a few percent of the same ratios):
+    //   1.3 tiles per CU  10,009 31.5 / 69.8, 39,409 172 / 280
+    //   2.3               12,493 42.4 / 52.1, 49,193 218 / 202
+    //   2.8               12,494 41.8 / 47.2, 24,598 94.6 / 90.0
+    //   3.4                7,862 22.2 / 24.2, 15,598 50.3 / 47.5, 30,709 123 / 89.6
+    //   5.5                3,931 11.0 / 12.7, 7,863 21.2 / 20.7, 15,601 47.0 / 35.6
+    //   8.3                7,864 19.4 / 20.2, 15,603 38.7 / 32.7
+    //   12.6              10,056 22.8 / 25.9, 19,952 48.5 / 42.6
+    //   16.7              10,057 22.0 / 25.4, 19,954 43.5 / 40.4
+    const double avg = (double)ctx->nnz / (double)std::max<int64_t>(ctx->nblocks, 1) / cus;
+    const double tiles = (double)n / cus;
+    if (tiles >= 1.5 && avg > std::max(40000.0 / tiles, 1000.0 * tiles)) return false;
     c.ns = kChainTable;
     int cap = tvs::kChainMaxTiles;
     while (cap > 0 && tvs::chain_lds_bytes(cap, c.ns) > (size_t)kChainLds) cap--;

@@ -33,3 +33,35 @@ def test_lanes_of_a_tile(dims, n, B, mode, chunk, threads):
                      tile_threads=64) as ctx:
         ctx.load_histories(h)
         assert ctx.debug_sweep() == (False, 64)
+
+
+@pytest.mark.parametrize("dims,n,B,mode,chain", [
+    ((64, 64, 1), 400_000, 204_800, "f32", True),          # few tiles: always
+    ((128, 128, 8), 204_800, 102_400, "f32", True),        # 1.3 tiles per CU
+    ((160, 160, 12), 51_200, 25_600, "q16", True),         # 2.8: up to 14,200 entries per CU
+    ((160, 160, 12), 204_800, 102_400, "q16", False),
+    ((200, 200, 10), 25_600, 12_800, "f32", True),         # 3.4: up to 11,600
+    ((200, 200, 10), 102_400, 51_200, "f32", False),
+    ((200, 200, 10), 102_400, 51_200, "otf", False),
+    ((200, 200, 16), 12_800, 6400, "f32", True),           # 5.5: up to 7,300
+    ((200, 200, 16), 51_200, 25_600, "f32", False),
+    ((256, 256, 32), 25_600, 12_800, "q16", True),         # 16.7: up to 16,700
+    ((256, 256, 32), 102_400, 51_200, "q16", False),
+    ((320, 320, 64), 6400, 3200, "f32", False),            # more tiles than the LDS holds
+])
+def test_chain_or_launches(dims, n, B, mode, chain):
+    grid, ph, h = scan(dims, n)
+    x0 = synth.initial_image(grid, ph)
+    out = []
+    for kernel in (0, 1):
+        print(f"chain or launches: {dims} B {B} {mode} sweep_kernel {kernel}", flush=True)
+        with tvs.Context(grid, block_size=B, path_mode=mode, sweep_kernel=kernel,
+                         time_sample=1_000_000) as ctx:
+            ctx.load_histories(h)
+            assert ctx.debug_sweep()[0] == (chain and kernel == 0)
+            ctx.set_image(x0)
+            ctx.iterate(1, 0.02, 1, 0.75, seed=11)
+            out.append(ctx.get_image())
+            blocks = -(-n // B)
+            assert ctx.stats()["k_samples"] == (blocks if chain and kernel == 0 else 0)
+    np.testing.assert_array_equal(out[0], out[1])
