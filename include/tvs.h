@@ -434,27 +434,33 @@ int tvs_server_get_counters(tvs_server *sv, tvs_server_counters *out);
 void tvs_server_destroy(tvs_server *sv);
 
 /* ------------------------------------------------------------------------
- * Autotuning of the launch shape.  Times every candidate shape (threads per
- * image-tile workgroup 64 / 128 / 256, one or two launches per DROP block)
- * on the first 1,024 blocks of the loaded histories, from the current image,
- * which is restored afterwards, and keeps the fastest for the context.  On
- * the fly a second stage then times whole sweeps (row formation beside the
- * chain) for the share of chunks formed at the row kernel's full occupancy
- * (tvs_config.fill_wide_pct: 0, 20, 40, 60, 80, 100) and keeps the fastest.
+ * Autotuning of the sweep.  Times every shape of the launches per block
+ * (threads per image-tile workgroup 64 / 128 / 256, one or two launches per
+ * DROP block) on the first 1,024 blocks of the loaded histories, from the
+ * current image, which is restored afterwards.  On the fly with several
+ * chunks a second stage then times whole sweeps (row formation beside the
+ * launches) for the share of chunks formed at the row kernel's full occupancy
+ * (tvs_config.fill_wide_pct: 0, 20, 40, 60, 80, 100).  Where the context can
+ * run many blocks per launch (sweep_kernel 0), that is timed last, on the same
+ * blocks or, against the best share, on whole sweeps.  The fastest is kept for
+ * the context, later loads included, and reported: what the context's sweeps
+ * run, and what tvs_config takes to run the same.
  * The block size B is a parameter of the method and is never changed (a
  * larger B is always faster per sweep, and changes the reconstruction).
  * With cache_path (a text file, created if missing) a shape measured before
  * for the same device, grid, history count, B and path mode is reused
- * without timing, and new measurements are appended.
+ * without timing, and new measurements are appended.  (A file's line that
+ * holds launches only is not reused where the context can run many blocks per
+ * launch.)
  * ------------------------------------------------------------------------ */
 typedef struct {
-    int32_t tile_threads;    /* chosen shape */
-    int32_t sweep_kernel;    /* 1: one launch per block, 2: two */
+    int32_t tile_threads;    /* chosen shape (0 with sweep_kernel 0) */
+    int32_t sweep_kernel;    /* 0: many blocks per launch, 1: one launch per block, 2: two */
     double ms_per_block;     /* its measured time per DROP block */
     int32_t from_cache;      /* 1: taken from the cache file */
     int32_t n_candidates;
-    int32_t cand_threads[8];
-    int32_t cand_sweep[8];
+    int32_t cand_threads[8]; /* as tile_threads */
+    int32_t cand_sweep[8];   /* as sweep_kernel */
     double cand_ms[8];       /* per block, per candidate */
     int32_t fill_wide_pct;   /* on the fly: chosen share of full-occupancy chunks, % */
     int32_t n_fill;          /* on the fly: shares timed (0 otherwise) */

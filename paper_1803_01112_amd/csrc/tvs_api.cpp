@@ -201,6 +201,7 @@ struct tvs_ctx {
     double big = 0.0, dot_max = 0.0;  // fixed-point ranges of the DROP kernels
     int threads = 256;              // threads per tile workgroup
     bool tuned = false;             // by tvs_autotune (else tile_lanes at every load)
+    bool launches = false;          // tvs_autotune: launches per block, not the chain
     int split = 0;                  // 1: two launches per block
     int bthreads = 256;             // batched DROP step: threads per workgroup
     int bgroup = 4;                 // batched DROP step: settings per pass through LDS
@@ -407,6 +408,9 @@ uint32_t *chain_dead(tvs_ctx *ctx)
 {
     return ctx->chain.bar + (tvs::kChainShards + ctx->chain.nreg) * 32;
 }
+
+// Whether sweeps take the chain.
+bool chain_on(const tvs_ctx *ctx) { return ctx->chain.on() && !ctx->launches; }
 
 // At the end of every call that allocates: what the call took from the chain
 // and has given back is the chain's again.
@@ -748,9 +752,10 @@ bool run_chain(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream_t 
     return true;
 }
 
-// One P_T sweep over the loaded histories (the first `limit` of them when
-// limit >= 0, a multiple of B: used to time launch shapes).
-int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
+// One P_T sweep over the loaded histories, by the chain where use_chain is set
+// and nothing stands against it (the first `limit` histories when limit >= 0, a
+// multiple of B: used to time launch shapes).
+int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, bool use_chain, int64_t limit = -1)
 {
     const int64_t B = ctx->cfg.block_size;
     const int64_t nh_run = (limit >= 0) ? std::min(limit, ctx->nh) : ctx->nh;
@@ -760,7 +765,7 @@ int run_sweep(tvs_ctx *ctx, double lambda, hipStream_t st, int64_t limit = -1)
     // a cooperative launch is not captured
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     const bool several = otf && ctx->nbuf > 1;
-    bool chain = ctx->chain.on() && hipStreamIsCapturing(st, &cap) == hipSuccess &&
+    bool chain = use_chain && ctx->chain.on() && hipStreamIsCapturing(st, &cap) == hipSuccess &&
                  cap == hipStreamCaptureStatusNone;
     // after a refused launch the rows of several chunks are formed beside
     // per-block launches again, for some sweeps
@@ -1928,7 +1933,7 @@ int tvs_iterate(tvs_ctx *ctx, const tvs_params *p, int32_t K, void *stream)
         }
         const long c1 = mark(ctx, st);
         span(ctx, 0, c0, c1);
-        rc = run_sweep(ctx, p->lambda, st);
+        rc = run_sweep(ctx, p->lambda, st, chain_on(ctx));
         if (rc) return rc;
         span(ctx, 1, c1, mark(ctx, st));
         ctx->k += 1;
@@ -2041,13 +2046,13 @@ int tvs_debug_sweep(tvs_ctx *ctx, int32_t what, int32_t out[2])
     if (!ctx->loaded) return fail(ctx, TVS_ESTATE, "no histories loaded");
     HIPCHK(hipSetDevice(ctx->cfg.device));
     auto &c = ctx->chain;
-    if (what == 1 && c.on()) {
+    if (what == 1 && c.mem) {
         const uint32_t one = 1;
         HIPCHK(hipStreamSynchronize(ctx->stream));
         HIPCHK(hipMemcpy(chain_dead(ctx), &one, sizeof(one), hipMemcpyHostToDevice));
     }
     if (what == 2) c.refuse = true;
-    out[0] = c.on() && !(c.refused > 0 && ctx->nbuf > 1);
+    out[0] = chain_on(ctx) && !(c.refused > 0 && ctx->nbuf > 1);
     out[1] = ctx->threads;
     return TVS_OK;
 }
@@ -2431,27 +2436,36 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
     hipDeviceProp_t prop;
     HIPCHK(hipGetDeviceProperties(&prop, ctx->cfg.device));
     const std::string key = tune_key(ctx, prop, "");
+    const bool has_chain = ctx->chain.planned && !ctx->chain.failed;
+    // what the choice leaves to the context: the chain or launches, and the
+    // launches' shape in either case (a captured sweep, a short budget)
+    auto keep = [&](int threads, int sweep, int pct, bool chain, double launch_ms, double chain_ms) {
+        ctx->threads = threads;
+        ctx->split = sweep == 2 ? 1 : 0;
+        ctx->fill_wide_pct = pct;
+        ctx->tuned = true;
+        ctx->launches = has_chain && !chain;     // without one, later loads decide anew
+        out->tile_threads = chain ? 0 : threads;
+        out->sweep_kernel = chain ? 0 : sweep;
+        out->ms_per_block = chain ? chain_ms : launch_ms;
+        out->fill_wide_pct = pct;
+    };
     if (cache_path) {
+        // the launches' shape and time, then whether the chain was the faster and
+        // its time.  A line without the last two was measured without a chain:
+        // where there is one, the choice is made anew
         cache_scan(cache_path, key, [&](const char *v) {
-            int th = 0, sw = 0, pct = -1;
-            double ms = 0;
-            const int got = std::sscanf(v, "%d %d %lf %d", &th, &sw, &ms, &pct);
-            if (got >= 3 && (th == 64 || th == 128 || th == 256) && (sw == 1 || sw == 2)) {
-                out->tile_threads = th;
-                out->sweep_kernel = sw;
-                out->ms_per_block = ms;
-                out->fill_wide_pct = (got == 4 && pct >= 0 && pct <= 100) ? pct
-                                                                           : ctx->fill_wide_pct;
+            int th = 0, sw = 0, pct = -1, ch = 0;
+            double ms = 0, cms = 0;
+            const int got = std::sscanf(v, "%d %d %lf %d %d %lf", &th, &sw, &ms, &pct, &ch, &cms);
+            if (got >= 3 && (th == 64 || th == 128 || th == 256) && (sw == 1 || sw == 2) &&
+                (got == 6 || !has_chain)) {
+                const int64_t use = (got >= 4 && pct >= 0 && pct <= 100) ? pct : ctx->fill_wide_pct;
+                keep(th, sw, (int)use, has_chain && ch != 0, ms, cms);
                 out->from_cache = 1;
             }
         });
-        if (out->from_cache) {
-            ctx->threads = out->tile_threads;
-            ctx->split = out->sweep_kernel == 2 ? 1 : 0;
-            ctx->fill_wide_pct = out->fill_wide_pct;
-            ctx->tuned = true;
-            return TVS_OK;
-        }
+        if (out->from_cache) return TVS_OK;
     }
     const int64_t B = ctx->cfg.block_size;
     // enough blocks that the candidates' differences stand above the spread
@@ -2460,8 +2474,8 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
     const int64_t nb = std::min<int64_t>(ctx->nblocks, 1024);
     out->fill_wide_pct = ctx->fill_wide_pct;
     if (nb == 0) {
-        out->tile_threads = ctx->threads;
-        out->sweep_kernel = ctx->split ? 2 : 1;
+        out->tile_threads = chain_on(ctx) ? 0 : ctx->threads;
+        out->sweep_kernel = chain_on(ctx) ? 0 : ctx->split ? 2 : 1;
         return TVS_OK;
     }
     HIPCHK(hipStreamSynchronize(ctx->fill_stream));
@@ -2470,116 +2484,111 @@ int tvs_autotune(tvs_ctx *ctx, double lambda, const char *cache_path, tvs_tune_r
     int rc = dalloc(ctx, &saved, (size_t)ctx->nvox);
     if (rc) return rc;
     HIPCHK(hipMemcpyAsync(saved, ctx->x, sizeof(double) * ctx->nvox, hipMemcpyDeviceToDevice, st));
+    // one sweep (of the first `limit` histories), its time in ms, and the image back
+    auto time_sweep = [&](bool chain, int64_t limit, float &ms) -> int {
+        ctx->tev_used = 0;
+        ctx->spans.clear();
+        const long a = mark(ctx, st);
+        const int r = run_sweep(ctx, lambda, st, chain, limit);
+        const long b = mark(ctx, st);
+        if (r) return r;
+        hipError_t e = hipMemcpyAsync(ctx->x, saved, sizeof(double) * ctx->nvox,
+                                      hipMemcpyDeviceToDevice, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = hipStreamSynchronize(ctx->fill_stream);
+        ms = 0;
+        if (e == hipSuccess && a >= 0 && b >= 0)
+            e = hipEventElapsedTime(&ms, ctx->tev[(size_t)a], ctx->tev[(size_t)b]);
+        if (e != hipSuccess)
+            return fail(ctx, TVS_EDEVICE, std::string("autotune: ") + hipGetErrorString(e));
+        return TVS_OK;
+    };
+    auto candidate = [&](int threads, int sweep, double ms) {
+        if (out->n_candidates >= 8) return;
+        out->cand_threads[out->n_candidates] = threads;
+        out->cand_sweep[out->n_candidates] = sweep;
+        out->cand_ms[out->n_candidates] = ms;
+        out->n_candidates++;
+    };
     const int ths[3] = {64, 128, 256};
     const int old_threads = ctx->threads, old_split = ctx->split;
-    // the candidates are launches per block, the shares those of chunks formed
-    // beside them (batches use both too); the chain goes on where it fits
-    struct ChainOff {
-        tvs_ctx *c;
-        bool planned;
-        ~ChainOff() { c->chain.planned = planned; }
-    } chain_off{ctx, ctx->chain.planned};
-    ctx->chain.planned = false;
+    const int64_t limit = std::min(nb * B, ctx->nh);
     double best = 1e300;
-    int nc = 0;
+    int best_threads = 0, best_sweep = 0;
     for (int sw = 1; sw <= 2 && rc == TVS_OK; sw++) {
         for (int ti = 0; ti < 3 && rc == TVS_OK; ti++) {
             ctx->threads = ths[ti];
             ctx->split = sw == 2 ? 1 : 0;
             double tbest = 1e300;
             for (int rep = 0; rep < 3 && rc == TVS_OK; rep++) {
-                ctx->tev_used = 0;
-                ctx->spans.clear();
-                long a = mark(ctx, st);
-                rc = run_sweep(ctx, lambda, st, std::min(nb * B, ctx->nh));
-                long b = mark(ctx, st);
-                if (rc) break;
-                hipError_t e = hipMemcpyAsync(ctx->x, saved, sizeof(double) * ctx->nvox,
-                                              hipMemcpyDeviceToDevice, st);
-                if (e == hipSuccess) e = hipStreamSynchronize(st);
-                if (e == hipSuccess) e = hipStreamSynchronize(ctx->fill_stream);
                 float ms = 0;
-                if (e == hipSuccess && a >= 0 && b >= 0)
-                    e = hipEventElapsedTime(&ms, ctx->tev[(size_t)a], ctx->tev[(size_t)b]);
-                if (e != hipSuccess) {
-                    rc = fail(ctx, TVS_EDEVICE, std::string("autotune: ") + hipGetErrorString(e));
-                    break;
-                }
+                rc = time_sweep(false, limit, ms);
                 if (rep > 0) tbest = std::min(tbest, (double)ms / nb);   // rep 0 warms up
             }
             if (rc) break;
-            if (nc < 8) {
-                out->cand_threads[nc] = ths[ti];
-                out->cand_sweep[nc] = sw;
-                out->cand_ms[nc] = tbest;
-                nc++;
-            }
+            candidate(ths[ti], sw, tbest);
             if (tbest < best) {
                 best = tbest;
-                out->tile_threads = ths[ti];
-                out->sweep_kernel = sw;
-                out->ms_per_block = tbest;
+                best_threads = ths[ti];
+                best_sweep = sw;
             }
         }
     }
-    out->n_candidates = nc;
-    if (rc || best == 1e300) {
-        dfree(ctx, &saved, (size_t)ctx->nvox);
-        ctx->tev_used = 0;
-        ctx->spans.clear();
-        ctx->timed = false;
-        ctx->threads = old_threads;
-        ctx->split = old_split;
-        return rc ? rc : fail(ctx, TVS_EDEVICE, "autotune: no candidate ran");
-    }
-    ctx->threads = out->tile_threads;
-    ctx->split = out->sweep_kernel == 2 ? 1 : 0;
-    ctx->tuned = true;
     // on the fly: whole sweeps (the row formation beside the launches) for the
     // share of chunks formed at the row kernel's full occupancy; with one
     // chunk the share does not matter
-    const int64_t nchunks = (ctx->nh + ctx->chunk - 1) / ctx->chunk;
-    if (ctx->cfg.path_mode == TVS_PATH_ON_THE_FLY && nchunks > 1) {
+    const bool several = ctx->cfg.path_mode == TVS_PATH_ON_THE_FLY && ctx->chunk_base.size() > 2;
+    const int old_pct = ctx->fill_wide_pct;
+    int pct = old_pct;
+    double pbest = 1e300;
+    if (!rc && several) {
         const int pcts[6] = {0, 20, 40, 60, 80, 100};
-        const int old_pct = ctx->fill_wide_pct;
-        double pbest = 1e300;
+        ctx->threads = best_threads;
+        ctx->split = best_sweep == 2 ? 1 : 0;
         for (int pi = 0; pi < 6 && rc == TVS_OK; pi++) {
             ctx->fill_wide_pct = pcts[pi];
-            ctx->tev_used = 0;
-            ctx->spans.clear();
-            long a = mark(ctx, st);
-            rc = run_sweep(ctx, lambda, st);
-            long b = mark(ctx, st);
-            if (rc) break;
-            hipError_t e = hipMemcpyAsync(ctx->x, saved, sizeof(double) * ctx->nvox,
-                                          hipMemcpyDeviceToDevice, st);
-            if (e == hipSuccess) e = hipStreamSynchronize(st);
-            if (e == hipSuccess) e = hipStreamSynchronize(ctx->fill_stream);
             float ms = 0;
-            if (e == hipSuccess && a >= 0 && b >= 0)
-                e = hipEventElapsedTime(&ms, ctx->tev[(size_t)a], ctx->tev[(size_t)b]);
-            if (e != hipSuccess) {
-                rc = fail(ctx, TVS_EDEVICE, std::string("autotune: ") + hipGetErrorString(e));
-                break;
-            }
+            rc = time_sweep(false, -1, ms);
+            if (rc) break;
             out->cand_pct[out->n_fill] = pcts[pi];
             out->cand_sweep_ms[out->n_fill] = ms;
             out->n_fill++;
             if (ms < pbest) {
                 pbest = ms;
-                out->fill_wide_pct = pcts[pi];
+                pct = pcts[pi];
             }
         }
-        ctx->fill_wide_pct = rc ? old_pct : out->fill_wide_pct;
+    }
+    // the chain, where its workspace is there beside the saved image: on the
+    // blocks that timed the launches, or against the best share's whole sweep
+    double cbest = 1e300;
+    if (!rc && ctx->chain.on()) {
+        ctx->chain.refused = 0;
+        for (int rep = 0; rep < 3 && rc == TVS_OK; rep++) {
+            float ms = 0;
+            rc = time_sweep(true, several ? -1 : limit, ms);
+            if (ctx->chain.refused > 0) {       // launches ran instead
+                cbest = 1e300;
+                break;
+            }
+            if (rep > 0) cbest = std::min(cbest, (double)ms / (several ? ctx->nblocks : nb));
+        }
+        if (!rc && cbest < 1e300) candidate(0, 0, cbest);
     }
     dfree(ctx, &saved, (size_t)ctx->nvox);
     ctx->tev_used = 0;
     ctx->spans.clear();
     ctx->timed = false;
+    ctx->threads = old_threads;
+    ctx->split = old_split;
+    ctx->fill_wide_pct = old_pct;
     if (rc) return rc;
+    const bool chain = cbest < 1e300 && cbest <= (several ? pbest / (double)ctx->nblocks : best);
+    keep(best_threads, best_sweep, pct, chain, best, cbest);
     char vals[128];
-    std::snprintf(vals, sizeof(vals), "%d %d %.6f %d", out->tile_threads, out->sweep_kernel,
-                  out->ms_per_block, out->fill_wide_pct);
+    int len = std::snprintf(vals, sizeof(vals), "%d %d %.6f %d", best_threads, best_sweep, best, pct);
+    if (cbest < 1e300)
+        std::snprintf(vals + len, sizeof(vals) - (size_t)len, " %d %.6f", chain ? 1 : 0, cbest);
     cache_append(cache_path, key, vals);
     return TVS_OK;
 }
