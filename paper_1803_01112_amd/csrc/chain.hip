@@ -811,7 +811,7 @@ __global__ void __launch_bounds__(NT) k_chain(ChainArgs A)
 template <typename CH>
 const void *chain_kernel(bool split)
 {
-    return split ? (const void *)k_chain<512, 6, CH, true> : (const void *)k_chain<1024, 4, CH, false>;
+    return split ? (const void *)k_chain<kChainSplitThreads, 6, CH, true> : (const void *)k_chain<1024, 4, CH, false>;
 }
 
 }  // namespace
@@ -835,7 +835,7 @@ hipError_t launch_chain(const ChainArgs &a, hipStream_t stream)
     arg.corr_small = std::min(a.big, 1024.0);          // |r a| 2^40 below 2^51
     void *args[] = {&arg};
     return hipLaunchCooperativeKernel(k, dim3((unsigned)(a.nreg * a.parts)),
-                                      dim3(split ? 512 : 1024), args, (unsigned)lds, stream);
+                                      dim3(split ? kChainSplitThreads : 1024), args, (unsigned)lds, stream);
 }
 
 }  // namespace tvs

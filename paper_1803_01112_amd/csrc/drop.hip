@@ -16,7 +16,7 @@
 //     in LDS and written back once;
 //   dots (block b): every entry multiplies its chord by the updated voxel
 //     value in LDS; within a wavefront the products of one row (consecutive
-//     in the list) are summed over their run with shuffles, and one atomic
+//     in the list) are summed over their run (by DPP), and one atomic
 //     per run adds the run's sum to the row's dot product.
 // Both halves of one step touch only the workgroup's own tile of x, so one
 // launch per block does both (the launch boundary is the only device-wide
@@ -145,7 +145,7 @@ template <int NT, typename CH>
 __device__ void tile_dots(const TileBlock &C, int64_t c0, int64_t c1, const Ent &e0,
                           const TileLds &L, double dot_max, uint32_t *err)
 {
-    // every thread runs the same number of rounds (the shuffles are uniform)
+    // every thread runs the same number of rounds (the sums take every lane)
     uint32_t m = e0.m;
     float a = e0.a;
     bool ok = e0.ok;

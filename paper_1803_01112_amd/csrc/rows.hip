@@ -96,7 +96,7 @@ __device__ inline double quot_rn(double a, double b)
     return fma(fma(-b, q, a), y, q);
 }
 
-// sqrt(x) rounded to nearest, x > 0: a coupled Newton step from the
+// sqrt(x) rounded to nearest, x > 0: one step of Goldschmidt's iteration from the
 // hardware's 1 / sqrt(x) for g -> sqrt(x) and h -> 1 / (2 sqrt(x)), then two
 // corrections of g by its exact residual.
 __device__ inline double sqrt_rn(double x)
@@ -1060,7 +1060,6 @@ k_hull_decide(GridDev g, const uint32_t *in_cnt, const uint32_t *out_cnt, uint32
     }
 }
 
-// dst[b] = src[b * stride] for b = 0 .. n - 1
 // Longest row and number of empty rows: stat[0], stat[1] (cleared before).
 __global__ void __launch_bounds__(kThreads) k_row_stats(const int32_t *nnz, int64_t n, uint32_t *stat)
 {
@@ -1142,6 +1141,7 @@ k_row_order(const int32_t *nnz, int64_t n, int64_t B, int64_t nblocks,
     }
 }
 
+// dst[b] = src[b * stride] for b = 0 .. n - 1
 __global__ void __launch_bounds__(kThreads)
 k_pick(const int64_t *src, int64_t stride, int64_t n, int64_t *dst)
 {

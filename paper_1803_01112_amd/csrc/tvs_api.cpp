@@ -153,8 +153,9 @@ struct tvs_ctx {
     double *x = nullptr, *g = nullptr;
     double *x0 = nullptr;           // initial iterate, the starting image of batches
     float *xio = nullptr;           // float32 staging of the image at the ABI
-    double *part = nullptr, *scal = nullptr;
-    uint32_t *ticket = nullptr;
+    double *part = nullptr;         // partial sums of ||g||^2
+    double *dec = nullptr;          // checked step: step scale, accepted
+    uint32_t *ticket = nullptr;     // checked step: last-workgroup counter
     int64_t nparts = 0;
     uint32_t *flags = nullptr;      // kNumFlags device flags
     long long *dot = nullptr;       // 3 x B fixed-point row dot products
@@ -896,13 +897,13 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
     std::vector<int32_t> reg;
     const int64_t B = ctx->cfg.block_size;
     if (ctx->cfg.sweep_kernel != 0 || ctx->cfg.tile_threads != 0 || B > tvs::kChainMaxB) return false;
-    int cus = 0, coop = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->cfg.device) != hipSuccess ||
-        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, ctx->cfg.device) != hipSuccess) {
+    const int cus = ctx->cus;
+    int coop = 0;
+    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, ctx->cfg.device) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    if (!coop || cus < 1) return false;
+    if (!coop) return false;
     // On the fly too: the rows of all the buffers' chunks are formed first, three
     // waves to a SIMD, then the chain runs over them.  The two do not fit a CU
     // together, and each alone is so much faster than beside the other that row
@@ -971,7 +972,7 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
         for (int i = 0; i <= n; i++) reg.push_back(i);
         // few tiles: several workgroups per tile, as far as the busiest
         // tile's list of a block fills them
-        const double per = 2.0 * tvs::kChainThreads;
+        const double per = 2.0 * tvs::kChainSplitThreads;
         c.parts = std::max(1, std::min(std::min(cus / n, 32), (int)std::ceil((most - 64.0) / per)));
     } else {
         double lo = std::max(most, total / cus), hi = total + 1.0;
@@ -1360,8 +1361,8 @@ void tvs_destroy(tvs_ctx *ctx)
     dfree(ctx, &ctx->flags, (size_t)kNumFlags);
     dfree(ctx, &ctx->dot, (size_t)(3 * (int64_t)ctx->cfg.block_size));
     dfree(ctx, &ctx->part, (size_t)ctx->nparts);
-    dfree(ctx, &ctx->scal, (size_t)4);
-    dfree(ctx, &ctx->ticket, (size_t)4);
+    dfree(ctx, &ctx->dec, (size_t)2);
+    dfree(ctx, &ctx->ticket, (size_t)1);
     dfree(ctx, &ctx->sched, (size_t)1);
     dfree(ctx, &ctx->dlog, (size_t)kDevLogCap);
     dfree(ctx, &ctx->cpart, (size_t)tvs::tv_check_parts(ctx->gd));
@@ -1458,8 +1459,8 @@ int tvs_create(const tvs_grid *grid, const tvs_config *cfg_in, tvs_ctx **out)
     if (!rc) rc = dalloc(ctx, &ctx->flags, (size_t)kNumFlags);
     if (!rc) rc = dalloc(ctx, &ctx->dot, (size_t)(3 * (int64_t)cfg.block_size));
     if (!rc) rc = dalloc(ctx, &ctx->part, (size_t)ctx->nparts);
-    if (!rc) rc = dalloc(ctx, &ctx->scal, (size_t)4);
-    if (!rc) rc = dalloc(ctx, &ctx->ticket, (size_t)4);
+    if (!rc) rc = dalloc(ctx, &ctx->dec, (size_t)2);
+    if (!rc) rc = dalloc(ctx, &ctx->ticket, (size_t)1);
     if (!rc) rc = dalloc(ctx, &ctx->sched, (size_t)1);
     if (!rc) rc = dalloc(ctx, &ctx->dlog, (size_t)kDevLogCap);
     if (!rc) rc = dalloc(ctx, &ctx->cpart, (size_t)tvs::tv_check_parts(ctx->gd));
@@ -1495,8 +1496,8 @@ int tvs_create(const tvs_grid *grid, const tvs_config *cfg_in, tvs_ctx **out)
     if (e == hipSuccess) e = hipMemsetAsync(ctx->x0, 0, sizeof(double) * nvox, ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(ctx->g, 0, sizeof(double) * nvox, ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(ctx->flags, 0, sizeof(uint32_t) * kNumFlags, ctx->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(ctx->ticket, 0, sizeof(uint32_t) * 4, ctx->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(ctx->scal, 0, sizeof(double) * 4, ctx->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(ctx->ticket, 0, sizeof(uint32_t), ctx->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(ctx->dec, 0, sizeof(double) * 2, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) {
         tvs_destroy(ctx);
@@ -1528,9 +1529,9 @@ int tvs_load_histories(tvs_ctx *ctx, int64_t n, const tvs_histories *h, int on_d
     HIPCHK(hipStreamSynchronize(ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->fill_stream));
     // Allocations given back in this call serve its next ones of the same size
-    // (a new scan of the same shape, and the temporaries: an
-    // allocation and its release take 0.1 to 0.4 ms) and are freed at its end.  Work of any stream on the old ones ends first, as
-    // hipFree would have seen to.
+    // (a new scan of the same shape, and the temporaries: an allocation and its
+    // release take 0.1 to 0.4 ms) and are freed at its end.  Work of any stream
+    // on the old ones ends first, as hipFree would have seen to.
     if (ctx->hist) HIPCHK(hipDeviceSynchronize());
     struct Recycle {
         tvs_ctx *c;
@@ -1883,7 +1884,7 @@ int tvs_iterate(tvs_ctx *ctx, const tvs_params *p, int32_t K, void *stream)
         ctx->spans.clear();
         ctx->timed = true;
     }
-    const tvs::CheckBuffers cb{ctx->cpart, ctx->ticket + 1, ctx->scal + 2};
+    const tvs::CheckBuffers cb{ctx->cpart, ctx->ticket, ctx->dec};
     const double check_alpha = (p->variant == TVS_OTVS) ? 0.5 : p->alpha;
     if (checked && K > 0 && !ctx->dev_sched) {
         HIPCHK(tvs::launch_sched_set(ctx->sched, ctx->ell, ctx->rng, st));

@@ -205,7 +205,6 @@ inline int64_t hull_full_words(const GridDev &g)
 hipError_t launch_hull_decide(const GridDev &g, const uint32_t *in_cnt, const uint32_t *out_cnt,
                               uint32_t min_in, uint32_t max_out, uint8_t *hull, double *mask,
                               hipStream_t stream);
-// dst[b] = src[b * stride] for b < n.
 // Initial iterate (fbp.hip): binning, Ram-Lak filter, backprojection,
 // in-slice median (radius 0..2; 0 only narrows the image to float32).
 // slots: a sum and a count per bin (16 B); the filter writes the means to p and
@@ -226,6 +225,7 @@ hipError_t launch_row_stats(const int32_t *nnz, int64_t n, uint32_t *stat, hipSt
 // Histories of each DROP block by decreasing row length (stat as above).
 hipError_t launch_row_order(const int32_t *nnz, int64_t n, int64_t B, const uint32_t *stat,
                             int32_t *order, hipStream_t stream);
+// dst[b] = src[b * stride] for b < n.
 hipError_t launch_pick(const int64_t *src, int64_t stride, int64_t n, int64_t *dst,
                        hipStream_t stream);
 // Fills the entry-side table of m for depths j = 0 .. nj - 1 (3 doubles each).
@@ -298,7 +298,7 @@ hipError_t launch_tile_totals(const uint32_t *cnt, int64_t nblocks, int64_t ntil
 // The DROP chain of many blocks as one resident kernel: nreg regions of
 // consecutive dispatch slots (at most tmax image tiles each), `parts`
 // workgroups per region (more than one only when every region is one tile).
-constexpr int kChainThreads = 512;
+constexpr int kChainSplitThreads = 512;   // lanes of a workgroup that shares its region
 constexpr int kChainShards = 16;          // counters of the device-wide barrier, 32 words apart
 constexpr int kChainMaxTiles = 32;        // tiles of a region (5 bits of a packed entry)
 constexpr int64_t kChainMaxB = (1 << 18) - 1;   // rows of a block (18 bits of a packed entry)
