@@ -234,9 +234,10 @@ k_drop_tile_batch(DropTileArgs A, int S, int64_t nvox, const double *lambda)
         for (int64_t q = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * NT + t;
              q < A.B * S; q += (int64_t)gridDim.x * gridDim.y * NT)
             A.zero[q] = 0;
-    // workgroup x takes tile tiles[x]; its lists' bounds at [slot]
-    const int64_t T = A.tiles[blockIdx.x];
-    const int64_t slot = A.slot_of ? A.slot_of[T] : (int64_t)blockIdx.x;
+    // workgroup x takes dispatch slot x (or slots[x]): its lists' bounds at
+    // [slot], its tile act[slot]
+    const int64_t slot = A.slots ? A.slots[blockIdx.x] : (int64_t)blockIdx.x;
+    const int64_t T = A.tiles[slot];
     int64_t p0 = 0, p1 = 0, c0 = 0, c1 = 0;
     if (A.P.valid) {
         p0 = A.P.toff[slot];

@@ -173,9 +173,11 @@ struct tvs_ctx {
     uint64_t *segtab = nullptr;     // nseg: global entry index of each segment's first entry
     int64_t nseg = 0;
     int64_t *bt_off = nullptr;      // nblocks * nact + 1 list starts, slots in order per block
-    int32_t *act = nullptr;         // tiles that some block's lists cross, the busiest first
-    int32_t *slot_of = nullptr;     // ntiles: tile -> slot, -1 for a tile no list crosses
-    bool by_region = false;         // slots in the chain's order (else slot i is tile act[i])
+    int32_t *act = nullptr;         // tiles that some block's lists cross (slot -> tile)
+    int32_t *slot_of = nullptr;     // ntiles: while lists are laid out, tile -> slot, -1 for a
+                                    // tile no list crosses; then, by_region, the slots by
+                                    // decreasing entries (launches per block)
+    bool by_region = false;         // slots in the order of the chain's regions
     int64_t nact = 0;
     int64_t nblocks = 0;
     // entries: the store, or a ring of chunk buffers on the fly
@@ -246,10 +248,9 @@ struct tvs_ctx {
                                     // (rows of several chunks on the fly)
         bool refuse = false;        // tvs_debug_sweep: the next launch counts as refused
         int nreg = 0, parts = 1, tmax = 0, ns = 0;
-        std::vector<int32_t> tab;   // first slot of each region (nreg + 1), then slot -> tile
+        std::vector<int32_t> first; // first slot of each region (nreg + 1)
         // device workspace, given back when a call needs its room (dalloc, chain_restore)
-        int32_t *reg = nullptr;     // tab's two parts
-        int32_t *act = nullptr;
+        int32_t *reg = nullptr;     // first, on the device
         uint32_t *bar = nullptr;    // barrier counters: all workgroups', then one per region;
                                     // behind them the mark of a wait that timed out
         uint8_t *exch = nullptr;    // exchange records of the workgroups (parts > 1)
@@ -372,29 +373,28 @@ void chain_release(tvs_ctx *ctx)
     ctx->recycle = false;
     dfree(ctx, &c.mem, c.bytes);
     ctx->recycle = recycle;
-    c.reg = c.act = nullptr;
+    c.reg = nullptr;
     c.bar = nullptr;
     c.exch = nullptr;
 }
 
 // Forms the chain's workspace again where it is missing and there is room:
-// counters and exchange records (cleared), then the tables.
+// counters and exchange records (cleared), then the regions.
 void chain_restore(tvs_ctx *ctx)
 {
     auto &c = ctx->chain;
     if (!c.planned || c.failed || c.mem || ctx->bytes + c.bytes > ctx->budget) return;
     const std::string err = ctx->err;
     const size_t nbar = chain_bar_bytes(c.nreg);
-    const size_t ntab = 4 * c.tab.size(), clear = c.bytes - ntab;
+    const size_t nfirst = 4 * c.first.size(), clear = c.bytes - nfirst;
     if (dalloc(ctx, &c.mem, c.bytes) == TVS_OK) {
         c.bar = reinterpret_cast<uint32_t *>(c.mem);
         c.exch = c.mem + nbar;
         c.reg = reinterpret_cast<int32_t *>(c.mem + clear);
-        c.act = c.reg + c.nreg + 1;
         c.epoch = c.sub_epoch = 0;
         hipError_t e = hipMemsetAsync(c.mem, 0, clear, ctx->stream);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(c.reg, c.tab.data(), ntab, hipMemcpyHostToDevice, ctx->stream);
+            e = hipMemcpyAsync(c.reg, c.first.data(), nfirst, hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -671,7 +671,7 @@ int launch_blocks(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream
         A.err = ctx->flags + kFlagRange;
         A.tiles = ctx->act;
         A.nact = ctx->nact;
-        A.slot_of = ctx->by_region ? ctx->slot_of : nullptr;
+        A.slots = ctx->by_region ? ctx->slot_of : nullptr;
         const bool samp = ctx->cfg.time_sample > 0 && has_c && b > b0 &&
                           b % ctx->cfg.time_sample == 0;
         tvs::KTimer kt;
@@ -705,7 +705,7 @@ bool run_chain(tvs_ctx *ctx, double lambda, int64_t b0, int64_t b1, hipStream_t 
     a.toff = ctx->bt_off;
     a.nact = ctx->nact;
     a.base = v.base;
-    a.act = c.act;
+    a.act = ctx->act;
     a.reg = c.reg;
     a.wepl = ctx->hist + 12 * ctx->nh;
     a.n2 = ctx->norm2;
@@ -988,10 +988,9 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
     c.nreg = (int)reg.size() - 1;
     c.tmax = 0;
     for (int r = 0; r < c.nreg; r++) c.tmax = std::max(c.tmax, reg[(size_t)r + 1] - reg[(size_t)r]);
-    c.tab = reg;
-    c.tab.insert(c.tab.end(), a.begin(), a.end());
+    c.first = reg;
     const size_t nexch = c.parts > 1 ? (size_t)c.nreg * c.parts * tvs::kChainExchBytes : 0;
-    c.bytes = chain_bar_bytes(c.nreg) + nexch + 4 * c.tab.size();
+    c.bytes = chain_bar_bytes(c.nreg) + nexch + 4 * c.first.size();
     c.planned = true;
     return true;
 }
@@ -1001,13 +1000,13 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
 // the DROP steps launch one workgroup per such tile only, in order of
 // decreasing entries over the scan, so that the longest lists are
 // dispatched first and do not trail the step.  Workgroup i of a step takes
-// tile busiest[i]; the lists are laid out in slot order, which is the same
-// or, where the chain runs, that of its regions (slot_of: tile -> slot, -1
-// for a tile no list crosses).  act is left in slot order, for the list
-// lengths; the caller then puts busiest there.  Both, like every argument of
-// the per-block launches, stay until the next load: a caller's graph may hold
-// them.  At least one tile is kept, so that a step always has a workgroup to
-// clear the next dot-product buffer.
+// slot i: tile act[i], whose lists are laid out in slot order (slot_of
+// inverts act; -1 for a tile no list crosses).  Where the chain runs the slots
+// are in the order of its regions instead, and workgroup i takes slot
+// busiest[i]; the caller puts busiest into slot_of's memory when that has
+// served.  Like every argument of the per-block launches it stays until the
+// next load: a caller's graph may hold it.  At least one tile is kept, so that
+// a step always has a workgroup to clear the next dot-product buffer.
 int build_active_tiles(tvs_ctx *ctx, const uint32_t *btc, std::vector<int32_t> &busiest,
                        hipStream_t st)
 {
@@ -1035,6 +1034,7 @@ int build_active_tiles(tvs_ctx *ctx, const uint32_t *btc, std::vector<int32_t> &
     if (ctx->by_region) a.swap(placed);
     std::vector<int32_t> inv((size_t)std::max<int64_t>(nt, 1), -1);
     for (size_t i = 0; i < a.size(); i++) inv[(size_t)a[i]] = (int32_t)i;
+    for (int32_t &t : busiest) t = inv[(size_t)t];
     rc = dalloc(ctx, &ctx->act, a.size());
     if (!rc) rc = dalloc(ctx, &ctx->slot_of, inv.size());
     if (rc) return rc;
@@ -1178,8 +1178,8 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
         cleanup();
         return fail(ctx, TVS_EDEVICE, std::string("tile lists: ") + hipGetErrorString(e));
     }
-    // the slots, then the lists of every block laid out in slot order: their
-    // bounds are at [b * nact + slot]
+    // the dispatch slots, then the lists of every block laid out in slot
+    // order: their bounds are at [b * nact + slot]
     std::vector<int32_t> busiest;
     rc = build_active_tiles(ctx, btc, busiest, st);
     if (!ctx->cfg.tile_threads && !ctx->tuned) ctx->threads = tile_lanes(ctx);
@@ -1191,15 +1191,14 @@ int build_tile_lists(tvs_ctx *ctx, hipStream_t st)
         return rc;
     }
     e = tvs::launch_slot_counts(btc, ctx->act, ctx->nact, ctx->nblocks, ctx->ntiles, sbc, st);
-    // from here on in dispatch order
-    if (e == hipSuccess && ctx->by_region)
-        e = hipMemcpyAsync(ctx->act, busiest.data(), sizeof(int32_t) * busiest.size(),
-                           hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
         e = tvs::launch_scan(reinterpret_cast<const int32_t *>(sbc), nsbc, ctx->bt_off, tmp, st);
     if (e == hipSuccess)
         e = tvs::launch_seg_dest(ctx->gd, n, B, ctx->seg_off, ctx->bt_off, ctx->slot_of,
                                  ctx->nact, ctx->segtab, ctx->flags + kFlagLists, st);
+    if (e == hipSuccess && ctx->by_region)
+        e = hipMemcpyAsync(ctx->slot_of, busiest.data(), sizeof(int32_t) * busiest.size(),
+                           hipMemcpyHostToDevice, st);
     // every block's lists must add up to the block's entries (the block
     // starts are gathered into the freed count buffer, then copied)
     std::vector<int64_t> starts((size_t)ctx->nblocks + 1);
@@ -2244,7 +2243,7 @@ int batch_cycle(tvs_ctx *ctx, int nmax, hipStream_t st)
         A.err = ctx->flags + kFlagRange;
         A.tiles = ctx->act;
         A.nact = ctx->nact;
-        A.slot_of = ctx->by_region ? ctx->slot_of : nullptr;
+        A.slots = ctx->by_region ? ctx->slot_of : nullptr;
         HIPCHK(tvs::launch_drop_tiles_batch(A, Bt.b, ctx->ntiles, ctx->bthreads, ctx->bgroup, st));
         if (otf && first_of_chunk && c >= 1 && c - 1 + NB < nchunks) {
             // the launch above was the last to read chunk c - 1's buffer
@@ -2678,7 +2677,7 @@ int tvs_autotune_batch(tvs_ctx *ctx, const tvs_params *p, int32_t S, const char 
                     A.err = ctx->flags + kFlagRange;
                     A.tiles = ctx->act;
                     A.nact = ctx->nact;
-                    A.slot_of = ctx->by_region ? ctx->slot_of : nullptr;
+                    A.slots = ctx->by_region ? ctx->slot_of : nullptr;
                     e = tvs::launch_drop_tiles_batch(A, Bt.b, ctx->ntiles, ctx->bthreads,
                                                      ctx->bgroup, st);
                 }

@@ -265,14 +265,13 @@ struct DropTileArgs {
     long long *zero = nullptr;  // dot accumulators to clear for block b + 1
     int64_t B = 0;
     uint32_t *err = nullptr;
-    // tiles that some block's lists cross (the others have no work in any
-    // step), the busiest first; non-null: workgroup i takes tile tiles[i],
-    // nact workgroups
+    // tiles by slot: those that some block's lists cross (the others have no
+    // work in any step); workgroup i of nact takes slot i, or slots[i]
     const int32_t *tiles = nullptr;
     int64_t nact = 0;
-    // slot of every tile's lists where the slots are laid out by region; null:
-    // workgroup i's lists are those of slot i
-    const int32_t *slot_of = nullptr;
+    // dispatch order of the slots (busiest first) where the slots themselves
+    // are laid out by region; null: slot order
+    const int32_t *slots = nullptr;
 };
 
 // Start/stop events of the kernels of one block (first and second launch);
