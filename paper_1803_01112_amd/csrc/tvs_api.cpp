@@ -51,6 +51,13 @@ constexpr int64_t kChainBlocks = 1024;
 // 18.05 beside each other and 14.8 with the chain; of 256x256x32 22.2, 21.7
 // and 17.8), so one in sixteen costs 0.2 to 0.5 %.
 constexpr int kRefusedSweeps = 15;
+// What a sweep by the chain costs beside its blocks, more than one by launches
+// (the cooperative launch, the image into the LDS and back): 38 against 14 us, and
+// half the difference again, since the estimates favour the chain on few blocks
+// (the first angles' lists are longer than the mean).  A sweep of few blocks is
+// launched (200x200x16 at B = 3,200, chain / launched: one block 45 / 22 us, four
+// 65 / 47, eight 91 / 79, sixteen 140 / 143).
+constexpr double kChainSweepUs = 36.0;
 constexpr int kChainTable = 2048;            // slots of its row table
 constexpr int kChainLds = 160 * 1024 - 256;  // LDS of a CU it may take
 
@@ -886,11 +893,38 @@ int count_rows(tvs_ctx *ctx, int64_t first, int64_t n, int64_t *row_off_dev, hip
     return TVS_OK;
 }
 
+// Time of a DROP block, us, launched and in the resident chain, for choosing
+// between them: n crossed tiles, `longest` the longest list of a block, `busiest`
+// the entries of the fullest region.  A launch's time goes with its longest list,
+// up to 8 tiles per CU being in work at once, and with all entries; the chain's
+// with a CU's entries, from some 3,000 on (the lanes hold 4,096 in registers, a
+// block more or less than the mean) at three times the price.  Least squares
+// over eleven grids of 0.5 to 17 tiles per CU at B = 16 to 102,400 (8 % and 4 %
+// mean error; the same for both stores).  Chain / launched, measured:
+//   tiles per CU 1.3    B = 800 4.9 / 6.1, 3,200 5.7 / 10.8, 25,600 31.5 / 69.8, 102,400 172 / 280
+//                2.8    800 5.1 / 6.3, 6,400 9.4 / 13.9, 25,600 41.8 / 47.2, 51,200 94.6 / 90.0
+//                3.4    6,400 11.6 / 14.0, 12,800 22.2 / 24.2, 25,600 50.3 / 47.5, 102,400 269 / 179
+//                5.5    800 5.3 / 6.7, 6,400 11.0 / 12.7, 12,800 21.2 / 20.7, 25,600 47.0 / 35.6
+//                16.7   800 5.5 / 8.8, 6,400 12.5 / 16.4, 12,800 22.0 / 25.4, 25,600 43.5 / 40.4
+double launch_us(const tvs_ctx *ctx, int n, double longest)
+{
+    const double t = (double)n / ctx->cus;
+    const double per_cu = (double)ctx->nnz / (double)std::max<int64_t>(ctx->nblocks, 1) / ctx->cus;
+    return 2.5 + 0.0064 * std::min(longest, 100.0) + 0.0043 * longest * std::max(1.0, t / 8.0) +
+           0.001 * per_cu + 1.4 * std::min(t, 1.0) + 0.15 * std::max(t - 1.0, 0.0);
+}
+double chain_us(int n, int cus, int parts, double busiest)
+{
+    const double e = busiest / parts;
+    return 4.7 + 0.0008 * e + (n < 8 * cus ? 0.0019 : 0.00115) * std::max(e - 3000.0, 0.0) +
+           0.00155 * std::max(e - 20000.0, 0.0) + (parts > 1 ? 2.2 : 0.0);
+}
+
 // Places the active tiles in regions of the resident chain (chain.hip), one
 // region per workgroup: reorders a (the tiles by slot) and describes them in
 // the context's chain.  False where the chain does not fit: explicit
 // launch shapes, blocks of more rows than a packed entry names, images whose
-// crossed tiles do not fit the device's LDS.
+// crossed tiles do not fit the device's LDS, sweeps that launches make faster.
 bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<int32_t> &a)
 {
     auto &c = ctx->chain;
@@ -904,32 +938,7 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
         return false;
     }
     if (!coop) return false;
-    // On the fly too: the rows of all the buffers' chunks are formed first, three
-    // waves to a SIMD, then the chain runs over them.  The two do not fit a CU
-    // together, and each alone is so much faster than beside the other that row
-    // formation overlapped with per-block launches loses: a cycle of 4 M rows of
-    // 200x200x16 takes 19.6 ms against 23.0, 60 M of 256x256x32 349 against 372,
-    // 2 M of 200x200x16 in chunks of 64 k 12.8 against 18.0, of 6,400 57 against 146.
     const int n = (int)a.size();
-    // Long lists: the chain's one workgroup per CU is bound by instruction issue,
-    // its time a block that of a CU's entries.  A launch's time goes with the
-    // longest list instead: up to 8 tiles per CU are in work at once, so the more
-    // of them share the entries, the shorter it is; past 8 it takes several
-    // rounds.  So the chain wins up to 40,000 entries per CU divided by the tiles
-    // per CU, or 1,000 times them; with few tiles always.  Measured, entries per
-    // CU and us a block of chain / launches (float32 store; the 6-byte store and
-    // rows on the fly within a few percent of the same ratios):
-    //   1.3 tiles per CU  10,009 31.5 / 69.8, 39,409 172 / 280
-    //   2.3               12,493 42.4 / 52.1, 49,193 218 / 202
-    //   2.8               12,494 41.8 / 47.2, 24,598 94.6 / 90.0
-    //   3.4                7,862 22.2 / 24.2, 15,598 50.3 / 47.5, 30,709 123 / 89.6
-    //   5.5                3,931 11.0 / 12.7, 7,863 21.2 / 20.7, 15,601 47.0 / 35.6
-    //   8.3                7,864 19.4 / 20.2, 15,603 38.7 / 32.7
-    //   12.6              10,056 22.8 / 25.9, 19,952 48.5 / 42.6
-    //   16.7              10,057 22.0 / 25.4, 19,954 43.5 / 40.4
-    const double avg = (double)ctx->nnz / (double)std::max<int64_t>(ctx->nblocks, 1) / cus;
-    const double tiles = (double)n / cus;
-    if (tiles >= 1.5 && avg > std::max(40000.0 / tiles, 1000.0 * tiles)) return false;
     c.ns = kChainTable;
     int cap = tvs::kChainMaxTiles;
     while (cap > 0 && tvs::chain_lds_bytes(cap, c.ns) > (size_t)kChainLds) cap--;
@@ -988,6 +997,22 @@ bool plan_chain(tvs_ctx *ctx, const std::vector<uint32_t> &entries, std::vector<
     c.nreg = (int)reg.size() - 1;
     c.tmax = 0;
     for (int r = 0; r < c.nreg; r++) c.tmax = std::max(c.tmax, reg[(size_t)r + 1] - reg[(size_t)r]);
+    double busiest = 0.0;       // entries of a block in the fullest region
+    for (int r = 0; r < c.nreg; r++) {
+        double sum = 0.0;
+        for (int i = reg[(size_t)r]; i < reg[(size_t)r + 1]; i++) sum += w[(size_t)i] - 64.0;
+        busiest = std::max(busiest, sum);
+    }
+    // On the fly too: the rows of all the buffers' chunks are formed first, three
+    // waves to a SIMD, then the chain runs over them.  The two do not fit a CU
+    // together, and each alone is so much faster than beside the other that row
+    // formation overlapped with per-block launches loses: a cycle of 4 M rows of
+    // 200x200x16 takes 19.6 ms against 23.0, 60 M of 256x256x32 349 against 372,
+    // 2 M of 200x200x16 in chunks of 64 k 12.8 against 18.0, of 6,400 57 against 146.
+    // So with several chunks the faster block decides, else a whole sweep's blocks.
+    const bool several = ctx->cfg.path_mode == TVS_PATH_ON_THE_FLY && ctx->chunk_base.size() > 2;
+    const double saved = launch_us(ctx, n, most - 64.0) - chain_us(n, cus, c.parts, busiest);
+    if (several ? saved <= 0.0 : saved * nb <= kChainSweepUs) return false;
     c.first = reg;
     const size_t nexch = c.parts > 1 ? (size_t)c.nreg * c.parts * tvs::kChainExchBytes : 0;
     c.bytes = chain_bar_bytes(c.nreg) + nexch + 4 * c.first.size();

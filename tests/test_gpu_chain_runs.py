@@ -31,14 +31,14 @@ def both(grid, h, x0, B, lam, **kw):
 
 
 @pytest.mark.parametrize("dims,n,B,mode,chunk", [
-    ((200, 200, 16), 70_000, 6400, "f32", 0),           # 5.5 tiles per CU, two rounds
-    ((256, 256, 32), 60_001, 12_800, "q16", 0),         # 17 tiles per CU, three rounds
-    ((160, 160, 12), 77_000, 25_600, "f16", 0),         # 2.8 tiles per CU, four rounds
+    ((200, 200, 16), 160_000, 6400, "f32", 0),          # 5.5 tiles per CU, two rounds
+    ((256, 256, 32), 256_001, 12_800, "q16", 0),        # 17 tiles per CU, three rounds
+    ((160, 160, 12), 204_700, 25_600, "f16", 0),        # 2.8 tiles per CU, four rounds
     ((160, 160, 12), 153_600, 25_600, "otf", 25_600),   # the same, chunks formed as one
     ((128, 128, 8), 250_000, 102_400, "f32", 0),        # up to five tiles, full row tables
     ((150, 150, 5), 300_000, 102_400, "q16", 0),        # about one tile, 20 rounds
-    ((64, 64, 1), 70_400, 64, "f32", 0),                # 1,100 blocks: two launches
-    ((200, 200, 8), 67_201, 48, "otf", 0),              # 1,401 of them, the last one ragged
+    ((64, 64, 1), 220_000, 200, "f32", 0),              # 1,100 blocks: two launches
+    ((128, 128, 4), 440_001, 400, "otf", 0),            # 1,101 of them, the last one ragged
 ])
 def test_chain_runs_and_equals_launches(dims, n, B, mode, chunk):
     grid = synth.centered_grid(*dims, 1.0, 1.0, 2.5)
@@ -50,12 +50,12 @@ def test_chain_runs_and_equals_launches(dims, n, B, mode, chunk):
     np.testing.assert_array_equal(a, b)
 
 
-@pytest.mark.parametrize("dims,B", [((200, 200, 16), 6400), ((160, 160, 12), 25_600),
-                                    ((256, 256, 32), 12_800)])
-def test_chain_runs_with_large_corrections(dims, B):
+@pytest.mark.parametrize("dims,n,B", [((200, 200, 16), 153_600, 6400),
+                                      ((160, 160, 12), 204_800, 25_600),
+                                      ((256, 256, 32), 256_000, 12_800)])
+def test_chain_runs_with_large_corrections(dims, n, B):
     """Rows that clip a corner of every slice by a short chord, from a zero image:
     corrections past 2^21 / B."""
-    n = 4 * B
     grid = synth.centered_grid(*dims, 1.0, 1.0, 2.5)
     h = synth.generate(grid, synth.catphan_like(grid, 0.75 * min(dims[0], dims[1])), n, 90, 3)
     rng = np.random.default_rng(1)

@@ -37,16 +37,20 @@ def test_lanes_of_a_tile(dims, n, B, mode, chunk, threads):
 
 @pytest.mark.parametrize("dims,n,B,mode,chain", [
     ((64, 64, 1), 400_000, 204_800, "f32", True),          # few tiles: always
+    ((64, 64, 2), 3200, 3200, "q16", True),
     ((128, 128, 8), 204_800, 102_400, "f32", True),        # 1.3 tiles per CU
-    ((160, 160, 12), 51_200, 25_600, "q16", True),         # 2.8: up to 14,200 entries per CU
+    ((160, 160, 12), 204_800, 25_600, "q16", True),        # 2.8
     ((160, 160, 12), 204_800, 102_400, "q16", False),
-    ((200, 200, 10), 25_600, 12_800, "f32", True),         # 3.4: up to 11,600
+    ((200, 200, 10), 256_000, 12_800, "f32", True),        # 3.4
     ((200, 200, 10), 102_400, 51_200, "f32", False),
     ((200, 200, 10), 102_400, 51_200, "otf", False),
-    ((200, 200, 16), 12_800, 6400, "f32", True),           # 5.5: up to 7,300
+    ((200, 200, 16), 160_000, 6400, "f32", True),          # 5.5
     ((200, 200, 16), 51_200, 25_600, "f32", False),
-    ((256, 256, 32), 25_600, 12_800, "q16", True),         # 16.7: up to 16,700
+    ((256, 256, 32), 320_000, 12_800, "q16", True),        # 16.7
     ((256, 256, 32), 102_400, 51_200, "q16", False),
+    ((200, 200, 16), 100_000, 3200, "f32", True),          # 32 blocks of it
+    ((200, 200, 16), 12_800, 3200, "f32", False),          # four
+    ((256, 256, 32), 3200, 3200, "otf", False),            # one
     ((320, 320, 64), 6400, 3200, "f32", False),            # more tiles than the LDS holds
 ])
 def test_chain_or_launches(dims, n, B, mode, chain):
@@ -65,3 +69,12 @@ def test_chain_or_launches(dims, n, B, mode, chain):
             blocks = -(-n // B)
             assert ctx.stats()["k_samples"] == (blocks if chain and kernel == 0 else 0)
     np.testing.assert_array_equal(out[0], out[1])
+
+
+def test_few_blocks_in_several_chunks():
+    """On the fly with several chunks the rows decide: formed as one, then the
+    chain, also where each group holds a few blocks."""
+    grid, ph, h = scan((200, 200, 16), 19_200)
+    with tvs.Context(grid, block_size=3200, chunk_histories=3200) as ctx:
+        ctx.load_histories(h)
+        assert ctx.debug_sweep()[0]

@@ -39,7 +39,7 @@ def cycle(ctx, x0):
     ((64, 64, 1), 30_000, 3200, "f32", 0),           # few tiles: the chain by far
     ((128, 128, 4), 60_000, 3200, "otf", 0),
     ((128, 128, 4), 60_000, 3200, "otf", 6400),      # several chunks: whole sweeps
-    ((200, 200, 16), 51_200, 6400, "q16", 0),
+    ((200, 200, 16), 160_000, 6400, "q16", 0),
 ])
 def test_reported_choice_is_what_runs(tmp_path, dims, n, B, mode, chunk):
     s = scan(dims, n)
@@ -100,14 +100,15 @@ def test_cached_choice_of_launches_leaves_the_chain(tmp_path):
 
 
 def test_choice_that_outlives_its_scan(tmp_path):
-    """Tuned on a scan without a chain (long lists), then a scan that has one;
+    """Tuned on a scan without a chain (few blocks), then a scan that has one;
     and a chain that was refused while it was timed."""
-    s = scan((200, 200, 10), 102_400)
-    with context(s, path_mode="f32", block_size=51_200) as ctx:
+    s = scan((200, 200, 10), 128_000)
+    few = {k: v[:6400] for k, v in s[1].items()}
+    with context((s[0], few, s[2]), path_mode="f32") as ctx:
         r = ctx.autotune(0.02)
         assert r["sweep_kernel"] in (1, 2) and cycle(ctx, s[2])[1] == 0
-        ctx.load_histories({k: v[:5000] for k, v in s[1].items()})
-        assert cycle(ctx, s[2])[1] == 1
+        ctx.load_histories(s[1])
+        assert cycle(ctx, s[2])[1] == 40
     s = scan((64, 64, 1), 30_000)
     cache = os.path.join(tmp_path, "tune.txt")
     with context(s, path_mode="f32") as ctx:
