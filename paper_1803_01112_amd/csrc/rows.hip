@@ -25,6 +25,7 @@ namespace {
 constexpr double kE0 = 13.6;     // MeV, Highland constant
 constexpr double kX0 = 360.8;    // mm, radiation length of water
 constexpr int kThreads = 256;
+constexpr int64_t kFewLines = 40000;   // hull lines that are bound by latency
 // Row kernels: at least 3 wavefronts per SIMD (two vertices evaluated side by
 // side fit only two: 14.0 against 11.5 ms for 4M rows of 200x200x16); the
 // tile-list kernel's kRoom instance holds 2, leaving room for DROP waves.
@@ -897,11 +898,23 @@ struct HullCounts {
     uint32_t in_sat, out_sat;
 };
 
-__device__ inline uint32_t hull_word(const uint32_t *full, int32_t p) { return full ? full[p >> 5] : 0u; }
+// What a line learns of voxel p as it enters it: the full-voxel bits that hold it
+// or, EARLY, its count.
+template <bool EARLY>
+__device__ inline uint32_t hull_word(const uint32_t *cnt, const uint32_t *full, int32_t p)
+{
+    if (EARLY) return __hip_atomic_load(cnt + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return full ? full[p >> 5] : 0u;
+}
 
-// Counts voxel p; word: the full-voxel bits that hold it.
+// Counts voxel p; word: what hull_word gave.
+template <bool EARLY>
 __device__ inline void hull_count(uint32_t *cnt, uint32_t word, uint32_t sat, int32_t p)
 {
+    if (EARLY) {
+        if (word < sat) atomicAdd(cnt + p, 1u);
+        return;
+    }
     if ((word >> (p & 31)) & 1u) return;
     if (__hip_atomic_load(cnt + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < sat)
         atomicAdd(cnt + p, 1u);
@@ -916,6 +929,7 @@ __device__ inline void hull_count(uint32_t *cnt, uint32_t word, uint32_t sat, in
 // of each other or of the end, they are formed as walk_segment forms them,
 // and a piece no longer than eps takes its voxel at the midpoint; a line that
 // touches a plane without crossing it does so all the way.
+template <bool EARLY>
 __device__ inline void hull_line(const GridDev &g, const double g0[3], const double g1[3],
                                  const HullCounts &h, bool in, bool out)
 {
@@ -950,12 +964,12 @@ __device__ inline void hull_line(const GridDev &g, const double g0[3], const dou
     }
     const double eps = loose ? 4.0 : 2.0e-8 / slow;
     double prev = 0.0;
-    // a voxel is counted one piece later: its bits arrive meanwhile
+    // a voxel is counted one piece later: its bits (its count) arrive meanwhile
     uint32_t win = 0u, wout = 0u;
     auto count_last = [&]() {
         if (last < 0) return;
-        if (in) hull_count(h.in_cnt, win, h.in_sat, last);
-        if (out) hull_count(h.out_cnt, wout, h.out_sat, last);
+        if (in) hull_count<EARLY>(h.in_cnt, win, h.in_sat, last);
+        if (out) hull_count<EARLY>(h.out_cnt, wout, h.out_sat, last);
     };
     for (;;) {
         const double lo = fmin(t[0], t[1]), hi = fmax(t[0], t[1]);
@@ -988,8 +1002,8 @@ __device__ inline void hull_line(const GridDev &g, const double g0[3], const dou
         if (inside && at != last) {
             count_last();
             last = at;
-            win = in ? hull_word(h.in_full, at) : 0u;
-            wout = out ? hull_word(h.out_full, at) : 0u;
+            win = in ? hull_word<EARLY>(h.in_cnt, h.in_full, at) : 0u;
+            wout = out ? hull_word<EARLY>(h.out_cnt, h.out_full, at) : 0u;
         }
         prev = tb;
         bool more = tb < 1.0;
@@ -1008,6 +1022,7 @@ __device__ inline void hull_line(const GridDev &g, const double g0[3], const dou
     count_last();
 }
 
+template <bool EARLY>
 __global__ void __launch_bounds__(kThreads)
 k_hull_counts(GridDev g, HistDev H, int64_t first, int64_t n, double wepl_in, double wepl_out,
               HullCounts h)
@@ -1024,7 +1039,7 @@ k_hull_counts(GridDev g, HistDev H, int64_t first, int64_t n, double wepl_in, do
     double g0[3], g1[3];
     to_grid(g, p0, g0);
     to_grid(g, p1, g1);
-    hull_line(g, g0, g1, h, in, out);
+    hull_line<EARLY>(g, g0, g1, h, in, out);
 }
 
 // A bit per voxel: its count has reached sat (in words [0, nw), out after them).
@@ -1332,7 +1347,13 @@ hipError_t launch_hull_counts(const GridDev &g, const HistDev &h, int64_t n, dou
             c.in_full = full;
             c.out_full = full + nw;
         }
-        hipLaunchKernelGGL(k_hull_counts, dim3((unsigned)((end - first + kThreads - 1) / kThreads)),
+        // Few lines wait for each voxel's count, so they read it a piece early
+        // (20,000 lines: 64x64 117 us a call against 123, 200x200x16 270
+        // against 311); with more of them a slice's counts are out of date by then
+        // and needless adds cost more (60,000 of 64x64 198 against 195, 200,000
+        // of 256x256 953 against 907).
+        auto kernel = n <= kFewLines ? k_hull_counts<true> : k_hull_counts<false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((end - first + kThreads - 1) / kThreads)),
                            dim3(kThreads), 0, stream, g, h, first, end, wepl_in, wepl_out, c);
         first = end;
     }
