@@ -896,27 +896,33 @@ struct HullCounts {
     uint32_t *in_cnt, *out_cnt;
     const uint32_t *in_full, *out_full;   // voxels at their value, a bit each (may be null)
     uint32_t in_sat, out_sat;
+    bool in_read, out_read;               // kByFlags: whether a count is read before it is added to
 };
 
+// How a voxel's count is added to: after a read of it (kRead), after one that is
+// requested a piece before (kEarly), or after a read where the flags say so.
+enum HullCount { kRead, kEarly, kByFlags };
+
 // What a line learns of voxel p as it enters it: the full-voxel bits that hold it
-// or, EARLY, its count.
-template <bool EARLY>
+// or, kEarly, its count.
+template <HullCount HOW>
 __device__ inline uint32_t hull_word(const uint32_t *cnt, const uint32_t *full, int32_t p)
 {
-    if (EARLY) return __hip_atomic_load(cnt + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (HOW == kEarly) return __hip_atomic_load(cnt + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return full ? full[p >> 5] : 0u;
 }
 
 // Counts voxel p; word: what hull_word gave.
-template <bool EARLY>
-__device__ inline void hull_count(uint32_t *cnt, uint32_t word, uint32_t sat, int32_t p)
+template <HullCount HOW>
+__device__ inline void hull_count(uint32_t *cnt, uint32_t word, uint32_t sat, bool read, int32_t p)
 {
-    if (EARLY) {
+    if (HOW == kEarly) {
         if (word < sat) atomicAdd(cnt + p, 1u);
         return;
     }
     if ((word >> (p & 31)) & 1u) return;
-    if (__hip_atomic_load(cnt + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < sat)
+    if ((HOW == kByFlags && !read) ||
+        __hip_atomic_load(cnt + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < sat)
         atomicAdd(cnt + p, 1u);
 }
 
@@ -929,7 +935,7 @@ __device__ inline void hull_count(uint32_t *cnt, uint32_t word, uint32_t sat, in
 // of each other or of the end, they are formed as walk_segment forms them,
 // and a piece no longer than eps takes its voxel at the midpoint; a line that
 // touches a plane without crossing it does so all the way.
-template <bool EARLY>
+template <HullCount HOW>
 __device__ inline void hull_line(const GridDev &g, const double g0[3], const double g1[3],
                                  const HullCounts &h, bool in, bool out)
 {
@@ -968,8 +974,8 @@ __device__ inline void hull_line(const GridDev &g, const double g0[3], const dou
     uint32_t win = 0u, wout = 0u;
     auto count_last = [&]() {
         if (last < 0) return;
-        if (in) hull_count<EARLY>(h.in_cnt, win, h.in_sat, last);
-        if (out) hull_count<EARLY>(h.out_cnt, wout, h.out_sat, last);
+        if (in) hull_count<HOW>(h.in_cnt, win, h.in_sat, h.in_read, last);
+        if (out) hull_count<HOW>(h.out_cnt, wout, h.out_sat, h.out_read, last);
     };
     for (;;) {
         const double lo = fmin(t[0], t[1]), hi = fmax(t[0], t[1]);
@@ -1002,8 +1008,8 @@ __device__ inline void hull_line(const GridDev &g, const double g0[3], const dou
         if (inside && at != last) {
             count_last();
             last = at;
-            win = in ? hull_word<EARLY>(h.in_cnt, h.in_full, at) : 0u;
-            wout = out ? hull_word<EARLY>(h.out_cnt, h.out_full, at) : 0u;
+            win = in ? hull_word<HOW>(h.in_cnt, h.in_full, at) : 0u;
+            wout = out ? hull_word<HOW>(h.out_cnt, h.out_full, at) : 0u;
         }
         prev = tb;
         bool more = tb < 1.0;
@@ -1022,7 +1028,7 @@ __device__ inline void hull_line(const GridDev &g, const double g0[3], const dou
     count_last();
 }
 
-template <bool EARLY>
+template <HullCount HOW>
 __global__ void __launch_bounds__(kThreads)
 k_hull_counts(GridDev g, HistDev H, int64_t first, int64_t n, double wepl_in, double wepl_out,
               HullCounts h)
@@ -1039,7 +1045,7 @@ k_hull_counts(GridDev g, HistDev H, int64_t first, int64_t n, double wepl_in, do
     double g0[3], g1[3];
     to_grid(g, p0, g0);
     to_grid(g, p1, g1);
-    hull_line<EARLY>(g, g0, g1, h, in, out);
+    hull_line<HOW>(g, g0, g1, h, in, out);
 }
 
 // A bit per voxel: its count has reached sat (in words [0, nw), out after them).
@@ -1339,7 +1345,7 @@ hipError_t launch_hull_counts(const GridDev &g, const HistDev &h, int64_t n, dou
     for (int q = 0; q < 3; q++) {
         const int64_t end = stage[q];
         if (end <= first) continue;
-        HullCounts c{in_cnt, out_cnt, nullptr, nullptr, in_sat, out_sat};
+        HullCounts c{in_cnt, out_cnt, nullptr, nullptr, in_sat, out_sat, true, true};
         if (first > 0) {
             hipLaunchKernelGGL(k_hull_full, dim3((unsigned)((nvox + kThreads - 1) / kThreads)),
                                dim3(kThreads), 0, stream, in_cnt, out_cnt, nvox, in_sat, out_sat,
@@ -1347,12 +1353,23 @@ hipError_t launch_hull_counts(const GridDev &g, const HistDev &h, int64_t n, dou
             c.in_full = full;
             c.out_full = full + nw;
         }
+        // A count is read before it is added to where most of the stage's lines
+        // would find it at its value: (nx + ny) / voxels of them pass through a voxel,
+        // about.  A read waits for the adds before it, so where these are many
+        // plain adds are faster (never filled: 8M lines of 256x256x32 61 ms
+        // against 98, 4M of 200x200 35 against 184; filled by the first line: 4M of
+        // 200x200 2.5 ms a call with the read, 3.1 without; 60,000 of 64x64 filled
+        // by four fifths of them 1.46 ms, 0.39 without).
+        const double hits = 0.125 * (double)(end - first) * ((double)g.nx + g.ny) / (double)nvox;
+        c.in_read = (double)in_sat < hits;
+        c.out_read = (double)out_sat < hits;
         // Few lines wait for each voxel's count, so they read it a piece early
         // (20,000 lines: 64x64 117 us a call against 123, 200x200x16 270
         // against 311); with more of them a slice's counts are out of date by then
         // and needless adds cost more (60,000 of 64x64 198 against 195, 200,000
         // of 256x256 953 against 907).
-        auto kernel = n <= kFewLines ? k_hull_counts<true> : k_hull_counts<false>;
+        auto kernel = !(c.in_read && c.out_read) ? k_hull_counts<kByFlags>
+                                                 : n <= kFewLines ? k_hull_counts<kEarly> : k_hull_counts<kRead>;
         hipLaunchKernelGGL(kernel, dim3((unsigned)((end - first + kThreads - 1) / kThreads)),
                            dim3(kThreads), 0, stream, g, h, first, end, wepl_in, wepl_out, c);
         first = end;
