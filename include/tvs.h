@@ -90,7 +90,8 @@ typedef struct {
     int32_t max_tries;       /* bound on the retries of one checked TV step; 0: 100000 */
     int32_t sweep_kernel;    /* 0: the library's choice: many DROP blocks per launch by
                                 workgroups that stay on the device, where the image's
-                                crossed tiles fit its LDS, else as 1;
+                                crossed tiles fit its LDS and the sweep is the faster
+                                for it, else as 1;
                                 1: one launch per DROP block (finish the previous block
                                 and form this block's dot products, tile by tile);
                                 2: the same work in two launches per block.
@@ -106,11 +107,12 @@ typedef struct {
     int32_t fill_wgs_per_cu; /* on-the-fly rows: cap on the workgroups per compute unit of
                                 the row formation that runs beside the DROP chain; 0 or < 0:
                                 no cap */
-    int32_t fill_wide_pct;   /* on-the-fly rows beside one launch per DROP block: percentage of the chunks formed at the row
-                                kernel's full occupancy (three waves per SIMD, which leaves a
-                                SIMD no room for DROP waves); the others are held at two
-                                waves per SIMD, with room for four DROP waves beside them;
-                                spread evenly over the sweep; < 0: the library's choice (0) */
+    int32_t fill_wide_pct;   /* on-the-fly rows beside one launch per DROP block: percentage
+                                of the chunks formed at the row kernel's full occupancy
+                                (three waves per SIMD, which leaves a SIMD no room for
+                                DROP waves); the others are held at two waves per SIMD,
+                                with room for four DROP waves beside them; spread evenly
+                                over the sweep; < 0: the library's choice (40) */
 } tvs_config;
 
 /* Fills *cfg with the defaults above (B = 3200, on-the-fly rows, log term on). */

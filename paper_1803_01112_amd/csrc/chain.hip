@@ -35,11 +35,14 @@
 // split each list: they exchange their sums of a block through memory (a
 // second, smaller barrier among them) and keep equal copies of the tile.
 //
-// A block is bound by latency and instruction issue, not by memory: 7.2 us at
-// 200x200x16, float32 store, B = 3200 (8.8 launched) are 0.7 residuals, 0.6
-// finish, 0.9 update, 1.1 dots, 0.8 flush and drain of the atomics, 2.1
-// preparing the next block and 1.0 more at the barrier.  Other blocks of
-// 3200: 6.7 against 13.0 us at 128x128x8, 10.5 against 100 at 64x64.
+// A block is bound by latency, not by memory: 6.4 us at 200x200x16, float32
+// store, B = 3200 (8.7 launched).  By lane 0's clock (whose reads add 0.35 us) 0.55
+// residuals, 0.6 finish, 0.8 update, 0.9 dots, 0.8 flush and drain of the
+// atomics, 2.4 preparing the next block and 0.65 more at the barrier.  Counters
+// over such blocks: the waves wait on memory or a barrier 55 % of their time, the
+// VALUs are busy 41 % of it, the LDS 31 % (18 % in bank conflicts); 5.3 MB move a
+// block, 4.1 of them its lists and rows' data.  Other blocks of 3200: 5.8
+// against 12.2 us at 128x128x8, 10.7 against 109 at 64x64.
 //
 // The launch is cooperative (all workgroups resident), and the library lets
 // the chains of several contexts follow one another; every wait is bounded and
